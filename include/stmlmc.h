@@ -82,9 +82,9 @@ typedef enum {
 /* One MLMC level: nodes per axis (nz = 1 in 2D; nx >= 3, ny >= 2 in 2D (a strip of one element
  * row with y-constant data is the 1D problem), ny >= 3 and nz >= 2 in 3D) and time steps.
  * smooth_sweeps and cheb_ratio override the problem's coarse_sweeps and
- * cheb_ratio for this level (0 keeps the problem's value); a tuner measures
- * them per level, since the best smoother degree depends on the slab
- * operator's spectrum, i.e. on h and dt. */
+ * cheb_ratio for this level (0 keeps the problem's value) and fix the degree
+ * and interval of its defect corrections (see mg_levels), which are otherwise
+ * taken from the slab operator's spectrum and adapted from slab to slab. */
 typedef struct {
   int nx, ny, nz;
   int m;
@@ -124,7 +124,7 @@ typedef struct {
   /* solver controls; 0 selects the default */
   double newton_tol;          /* max-norm Newton step per slab (u is O(1)): 1e-10; a slab stops when its
                                  step or the step predicted from the observed contraction is below it */
-  int newton_max;             /* Newton iterations per slab: 30 */
+  int newton_max;             /* Newton iterations per slab (defect corrections, at most 16, not counted): 30 */
   double gmres_rtol;          /* relative Krylov residual: 1e-10 (fp64), 1e-5 (mixed) */
   int gmres_restart;          /* Krylov dimension of one linear solve: 16, at most 30; an unfinished
                                  solve is continued by the next Newton step */
@@ -135,7 +135,10 @@ typedef struct {
                                  are rediscretised: element conductivity the mean of its children, the
                                  coarse grid's own fibre angles, reaction weights injected from the level's
                                  grid.  Restriction is full weighting (the transpose of Q1 interpolation).
-                                 A level with coarse grids is solved by one-workgroup teams */
+                                 A level with coarse grids is solved by one-workgroup teams.  On a
+                                 level without, Chebyshev-weighted, a Newton step is a defect
+                                 correction: the sweeps applied to the FP64 residual, no Krylov space;
+                                 a slab that these do not contract well goes on with GMRES */
   int smooth_steps;           /* weighted-Jacobi sweeps before and after the coarse correction: 2 */
   double smooth_omega;        /* fixed Jacobi weight (smoother 0): 0.7 */
   int coarse_sweeps;          /* weighted-Jacobi sweeps on the coarsest grid (the only grid when
@@ -175,9 +178,9 @@ typedef struct {
 /* Per-sample solver statistics (host array filled by stm_st_solve). */
 typedef struct {
   int status;                 /* stm_status of this sample */
-  int newton_max_per_slab;    /* largest Newton count of any time slab */
-  int64_t newton_iters;       /* Newton iterations summed over slabs */
-  int64_t krylov_iters;       /* Krylov iterations summed over all linear solves */
+  int newton_max_per_slab;    /* largest count of Newton steps and defect corrections of any time slab */
+  int64_t newton_iters;       /* Newton steps and defect corrections summed over slabs */
+  int64_t krylov_iters;       /* preconditioner applications: Krylov iterations and defect corrections */
   double final_step;          /* largest final max-norm Newton step over slabs */
   double device_seconds;      /* wall time of this sample on its workgroup(s) */
   double algorithmic_bytes;   /* bytes the solve's passes must move: each array a pass reads or
@@ -189,7 +192,8 @@ typedef struct {
                                  n nodes: 4 float64 words per Newton residual; per Krylov iteration j
                                  (0-based within its linear solve) 4 words for the Jacobian product,
                                  5 per smoother sweep (on every V-cycle grid, weighted by its nodes)
-                                 and 2j + 3 for the Arnoldi step, in the inner precision.  Passes the
+                                 and 2j + 3 for the Arnoldi step, in the inner precision; per defect
+                                 correction its sweeps alone.  Passes the
                                  kernel fuses are counted as the separate steps they replace */
   int64_t damped_steps;       /* Newton steps halved because the residual 2-norm grew (each halving
                                  costs one residual evaluation, counted in newton_iters) */

@@ -2,8 +2,8 @@
 
 The slab operators M/dt + K - M diag f'(u) of a level have a spectrum set by
 h and dt, so the best Jacobi sweep count K and Chebyshev interval ratio differ
-between levels: more sweeps make each preconditioner application dearer but
-cut Krylov (and, through the inexact-Newton forcing, Newton) iterations.  The
+between levels: more sweeps make each defect correction dearer but fewer of
+them are needed.  The
 tuner solves a batch of samples of each level with every candidate (one
 workgroup per sample, as in the MLMC launch), keeps the candidate with the
 smallest mean workgroup-seconds per sample among those whose samples all
@@ -29,11 +29,11 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 TUNING_DIR = os.path.join(HERE, "tuning")
 
-CANDIDATES = [(8, 10.0), (10, 10.0), (12, 10.0), (14, 10.0), (16, 10.0), (16, 20.0), (20, 10.0), (24, 10.0)]
-# 3D levels measured faster with wider Chebyshev intervals (ratio 20 against
-# 10 on the 65x65x17 slab), so their list spans ratios 10 to 30.
-CANDIDATES_3D = [(8, 10.0), (12, 10.0), (8, 20.0), (12, 20.0), (16, 20.0), (24, 20.0), (12, 30.0), (16, 30.0),
-                 (24, 30.0)]
+# (0, 0): degree and interval from the operator's spectrum, adapted from slab
+# to slab, which is within a few percent of the best fixed setting or ahead of
+# it on most levels.
+CANDIDATES = [(0, 0.0), (11, 7.0), (13, 9.0)]
+CANDIDATES_3D = [(0, 0.0), (12, 7.0), (20, 20.0)]
 TEAM_SIZES = (1, 2, 3, 4, 6, 8, 10, 12, 16, 24, 32)
 MAX_TEAM = 32
 LARGE_TEAM_SIZES = (8, 16, 24, 32)

@@ -12,7 +12,11 @@ LIB = os.path.join(HERE, "libstmlmc.so")
 CAL_LIB = os.path.join(HERE, "libstmcal.so")  # copy kernels for counter calibration (not the solver interface)
 BUILD_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["st_solver.hip", "kl_gemm.hip", "qoi_mlmc.hip", "stm_api.hip"]
+# (source, its own flags, object name): the solver's kernels are one object per
+# dimension and inner precision, which compile side by side
+SOURCES = [("st_solver.hip", ["-DSTM_SOLVER_DIM=%d" % d, "-DSTM_SOLVER_FP32=%d" % f], "st_solver_%d_%d" % (d, f))
+           for d in (3, 2) for f in (0, 1)]
+SOURCES += [(s, [], os.path.splitext(s)[0]) for s in ("st_launch.hip", "kl_gemm.hip", "qoi_mlmc.hip", "stm_api.hip")]
 
 # Packed-fp32 instructions stay off: the compiler otherwise forms them from
 # plain float code.
@@ -29,8 +33,8 @@ def hipcc():
     return path
 
 
-def _compile(src, extra=(), build_dir=BUILD_DIR):
-    obj = os.path.join(build_dir, os.path.splitext(src)[0] + ".o")
+def _compile(src, extra=(), build_dir=BUILD_DIR, name=None):
+    obj = os.path.join(build_dir, (name or os.path.splitext(src)[0]) + ".o")
     cmd = [hipcc()] + FLAGS + list(extra) + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -47,7 +51,7 @@ def build(verbose=False, lib=LIB, defines=(), build_dir=BUILD_DIR):
     os.makedirs(build_dir, exist_ok=True)
     extra = ["-D" + d for d in defines]
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(lambda src: _compile(src, extra, build_dir), SOURCES))
+        objs = list(ex.map(lambda s: _compile(s[0], s[1] + extra, build_dir, s[2]), SOURCES))
     tmp = lib + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -5,7 +5,14 @@
 // system is block lower bidiagonal, so Newton's method on it can be carried
 // out slab by slab in time order (block forward substitution, eq. system_C):
 // slab k is iterated with Newton steps A_k delta = -R_k until its correction is
-// below tolerance, given the converged slab k-1.  Each linear step is GMRES,
+// below tolerance, given the converged slab k-1.  On one grid a step is a defect
+// correction, delta = P(A_k) (-R_k) with P the Chebyshev iteration on the
+// spectrum of D^-1 A_k: the residual is evaluated anyway before the next step,
+// so a Krylov space would only repeat its work (per slab and at equal accuracy
+// 3 x 15 sweeps in 2D and 3 x 26 in 3D take the place of 60-70 and 100-120
+// inside GMRES with its products, dots and updates: 33^2 x 64 steps 20.5 -> 8.9
+// ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms, 65x65x17 x 32 x 16 98 -> 59 ms).
+// Where it does not contract, and with a V-cycle, the linear step is GMRES,
 // right-preconditioned by one geometric-multigrid V-cycle with weighted-Jacobi
 // smoothing on the slab operator A_k = M/dt + K - M diag f'(u_k) (with one
 // grid the V-cycle reduces to its smoothing sweeps).  The Jacobi weights are
@@ -115,6 +122,16 @@ struct SigmaOf<float> {
 constexpr int kPartStride = 16;       // doubles per member in the partials buffer
 constexpr double kMinStep = 1.0 / 64;  // smallest damped fraction of a Newton step
 constexpr unsigned kSpinLimit = 1u << 25;
+// Defect corrections by Chebyshev sweeps.  A slab keeps to them while each
+// contracts the residual by kContract; after kMaxFallbacks slabs in a row that
+// did not, the sample gives them up for GMRES.
+constexpr double kContract = 0.1;
+constexpr int kMaxFallbacks = 2;
+constexpr int kMaxCorrections = 16;  // per slab
+constexpr double kChebTol = 0.003;   // of newton_tol: predicted size of the next correction
+constexpr double kChebReduction = 1e-4;  // error reduction of a correction over the whole interval
+constexpr double kChebNarrow = 1.4;  // interval ratio between one step of narrowing and the next
+constexpr int kCorrectionCost = 5;   // residual and update of a correction, in sweeps
 
 template <int DIM>
 __device__ __forceinline__ void decode(const GridDev& g, int idx, int& i, int& j, int& k) {
@@ -177,6 +194,18 @@ __device__ __forceinline__ T apply_at(const GridDev& g, int i, int j, int k, FM 
 __device__ __forceinline__ double react(double u, double kr, double ar) { return kr * u * (u - ar) * (1.0 - u); }
 __device__ __forceinline__ double react_d(double u, double kr, double ar) {
   return kr * (-3.0 * u * u + 2.0 * (1.0 + ar) * u - ar);
+}
+
+// Weights 1 / xi_s, xi_s the roots of the degree-K Chebyshev polynomial
+// shifted to [a, b], ordered to alternate large and small roots.
+__device__ inline void chebyshev_weights(double a, double b, int K, double* w) {
+  const double th = 0.5 * (b + a), de = 0.5 * (b - a);
+  const double PI = 3.14159265358979323846;
+  for (int s = 0; s < K; ++s) {
+    const int r = (s % 2 == 0) ? s / 2 : K - 1 - s / 2;
+    const double xi = th + de * cos(PI * (2 * r + 1) / (2.0 * K));
+    w[s] = 1.0 / xi;
+  }
 }
 
 // MG: the launch contains a level with a multigrid hierarchy.  Without one the
@@ -376,18 +405,21 @@ struct Team {
   // body(idx, i, j, k, y, o0, o1, o2, o3) with o* the staged values at the
   // node.  Phases A and B read LDS only; every LDS array is laid out so that
   // consecutive lanes touch consecutive words.  Index decoding uses exact
-  // multiply-high division.  Ends with a team barrier.
+  // multiply-high division.
   // Grid l >= 1 (a coarse V-cycle grid, one-workgroup teams) is staged the
   // same way, with its own conductivities, fibre rows and tiles, every row
   // owned.
+  // publish = false leaves the closing team barrier to the reduction that
+  // the caller starts right after the pass.
   template <typename T, typename KV, typename MV, typename Body>
   __device__ __forceinline__ void staged(int l, const T* __restrict__ f0, const T* __restrict__ f1, const T* __restrict__ f2,
-                         const T* __restrict__ f3, KV kval, MV mval, Body body) const {
+                         const T* __restrict__ f3, KV kval, MV mval, Body body, bool publish = true) const {
     if constexpr (DIM == 3) {
       zmarch<T>(l, f0, f1, f2, f3, kval, mval, body);
     } else {
       staged_tiles<T>(l, f0, f1, f2, f3, kval, mval, body);
     }
+    if (G > 1 && publish) team_barrier();
   }
 
   // ---- z-marching pass (3D) -------------------------------------------------
@@ -415,7 +447,7 @@ struct Team {
   //   * a workgroup barrier, which also waits for the step's loads.
   // f0 and f1 are read from memory once per tile (plus the halo rows), f2, f3
   // and the conductivities once.  A stiffness argument kval = KScale{c} is
-  // folded into the element factors.  Ends with a team barrier.
+  // folded into the element factors.
   template <typename T, typename KV, typename MV, typename Body>
   __device__ __forceinline__ void zmarch(int l, const T* __restrict__ f0, const T* __restrict__ f1,
                                          const T* __restrict__ f2, const T* __restrict__ f3, KV kval, MV mval,
@@ -600,7 +632,6 @@ struct Team {
         s0 = s1;
       }
     }
-    if (G > 1) team_barrier();
   }
 
   // n dwords from global memory to LDS by direct-to-LDS loads: lane i of the
@@ -818,7 +849,6 @@ struct Team {
         __syncthreads();
       }
     }
-    if (G > 1) team_barrier();
   }
 
   // ---- per-sample operator data ----------------------------------------------
@@ -974,9 +1004,11 @@ struct Team {
   // the same operations in the same order as in the pass that owns them, so the
   // result equals two single sweeps.  x == null stands for the sweep from zero,
   // x = om0 b dinv, formed while staging (three sweeps in the pass).  out must
-  // not alias x.  Ends with a team barrier.
+  // not alias x.  last: fin(node, value) takes every result, and the closing
+  // team barrier is left to the caller's reduction.
+  template <typename Fin>
   __device__ __forceinline__ void jacobi_pair(const TI* __restrict__ x, const TI* __restrict__ b, TI* __restrict__ out, TI om0,
-                              TI om1, TI om2) const {
+                              TI om1, TI om2, bool last, Fin fin) const {
     static_assert(DIM == 2, "the fused sweep pair is 2D");
     using T = TI;
     constexpr int NV = 4;
@@ -1120,22 +1152,29 @@ struct Team {
           }
           const int o = (j - jr0) * nx + i;
           const T xn = lxs[o] + om * (lb[o] - y) * ld[o];
-          if (sweep == 0) lx1[o] = xn;
-          else out[j * nx + i] = xn;
+          if (sweep == 0) {
+            lx1[o] = xn;
+          } else {
+            out[j * nx + i] = xn;
+            if (last) fin(j * nx + i, xn);
+          }
         }
         __syncthreads();
       }
     }
-    if (G > 1) team_barrier();
+    if (G > 1 && !last) team_barrier();
   }
 
   // Every sweep of the smoother in one pass, for a one-workgroup team whose
   // grid fits one tile (2D): the mass weights, b, dinv, sigma and the fibre
   // rows are staged once; the first sweep (from x = 0) is om b dinv, the later
   // ones alternate between two LDS vectors, and the last is written to out.
-  // Each sweep takes the operations of a single sweep in the same order.  Ends
-  // with a workgroup barrier.
-  __device__ __forceinline__ void jacobi_resident(const TI* __restrict__ b, TI* __restrict__ out, int nc) const {
+  // Each sweep takes the operations of a single sweep in the same order; row
+  // is the weights' row of the omega table, fin as in jacobi_pair (every call
+  // is a last pass).  Ends with a workgroup barrier.
+  template <typename Fin>
+  __device__ __forceinline__ void jacobi_resident(const TI* __restrict__ b, TI* __restrict__ out, int nc, int row,
+                                                  Fin fin) const {
     static_assert(DIM == 2, "the resident smoother is 2D");
     using T = TI;
     constexpr int NV = 4;
@@ -1200,9 +1239,13 @@ struct Team {
     __syncthreads();
     // ---- sweep 1 from x = 0 ----
     {
-      const T om = wgt(0, 0);
+      const T om = wgt(row, 0);
       T* dst = nc == 1 ? out : lx0;
-      for (int q = threadIdx.x; q < nst; q += BLOCK) dst[q] = om * lb[q] * ld[q];
+      for (int q = threadIdx.x; q < nst; q += BLOCK) {
+        const T xn = om * lb[q] * ld[q];
+        dst[q] = xn;
+        if (nc == 1) fin(q, xn);
+      }
       __syncthreads();
     }
 #pragma unroll 1
@@ -1242,7 +1285,7 @@ struct Team {
       }
       __syncthreads();
       // ---- phase B: every node ----
-      const T om = wgt(0, s - 1);
+      const T om = wgt(row, s - 1);
       for (int q = threadIdx.x; q < nst; q += BLOCK) {
         const int j = fdiv(q, mnx);
         const int i = q - j * nx;
@@ -1262,8 +1305,12 @@ struct Team {
           }
         }
         const T xn = cur[q] + om * (lb[q] - y) * ld[q];
-        if (s == nc) out[q] = xn;
-        else nxt[q] = xn;
+        if (s == nc) {
+          out[q] = xn;
+          fin(q, xn);
+        } else {
+          nxt[q] = xn;
+        }
       }
       __syncthreads();
     }
@@ -1359,7 +1406,7 @@ struct Team {
         // pass each), and a single sweep when one is left.  Pass t (1-based) of
         // P writes buf[(P - t + 1) % 2]: the last one out0.
         if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
-          jacobi_resident(b0, out0, nc);
+          jacobi_resident(b0, out0, nc, 0, [](int, TI) {});
           return;
         }
         // With three or more sweeps the first pass runs sweeps 1 to 3 (the sweep
@@ -1368,7 +1415,7 @@ struct Team {
         const int P = nc - np - (nc >= 3 ? 1 : 0);
         int s, t;
         if (nc >= 3) {
-          jacobi_pair(nullptr, b0, buf[P % 2], wgt(0, 0), wgt(0, 1), wgt(0, 2));
+          jacobi_pair(nullptr, b0, buf[P % 2], wgt(0, 0), wgt(0, 1), wgt(0, 2), false, [](int, TI) {});
           s = 4;
         } else {
           jacobi(0, b0, nullptr, buf[P % 2], wgt(0, 0));
@@ -1376,7 +1423,8 @@ struct Team {
         }
         t = 2;
         for (; s + 1 <= nc; s += 2, ++t)
-          jacobi_pair(buf[(P - t + 2) % 2], b0, buf[(P - t + 1) % 2], TI(0), wgt(0, s - 1), wgt(0, s));
+          jacobi_pair(buf[(P - t + 2) % 2], b0, buf[(P - t + 1) % 2], TI(0), wgt(0, s - 1), wgt(0, s), false,
+                      [](int, TI) {});
         for (; s <= nc; ++s, ++t) jacobi(0, b0, buf[(P - t + 2) % 2], buf[(P - t + 1) % 2], wgt(0, s - 1));
       }
       return;
@@ -1408,6 +1456,106 @@ struct Team {
     }
   }
 
+  // One defect correction of the slab's Newton equation (single-grid levels):
+  // nc Chebyshev-weighted sweeps from x = 0 on A x = b with the weights of
+  // omega row 1, the last sweep handing every owned node's value to fin.  3D
+  // (nc even): with x1 the first sweep's result is in mgT(0) already, formed by
+  // the residual pass.  2D (nc odd): sweeps 1 to 3, then pairs.  Leaves the
+  // closing team barrier to the caller.
+  template <typename Fin>
+  __device__ __forceinline__ void chebyshev(const TI* __restrict__ b0, TI* __restrict__ out0, int nc, bool x1,
+                                            Fin fin) const {
+    TI* buf[2] = {mgT(0), out0};
+    if constexpr (DIM == 3) {
+      if (!x1) jacobi(0, b0, nullptr, buf[nc % 2], wgt(1, 0));
+      const TI* __restrict__ w = mgW(0);
+      const int n = L->g[0].n;
+#pragma unroll 1
+      for (int s = 2; s <= nc; ++s) {
+        const TI* x = buf[(nc - s) % 2];
+        TI* out = buf[(nc - s + 1) % 2];
+        const TI om = wgt(1, s - 1);
+        const bool last = s == nc;
+        bytes = uni(bytes + (5.0 * sizeof(TI) * n + dbytes(0)));
+        staged<TI>(
+            0, x, w, b0, dinv, KScale<TI>{TI(prm.theta)}, [](TI a, TI ww) { return ww * a; },
+            [&](int idx, int, int, int, TI y, TI xo, TI, TI bo, TI dio) {
+              const TI xn = xo + om * (bo - y) * dio;
+              gmem(out)[idx] = xn;
+              if (last) fin(idx, xn);
+            },
+            !last);
+      }
+    } else {
+      if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
+        jacobi_resident(b0, out0, nc, 1, fin);
+        return;
+      }
+      const int P = (nc - 1) / 2;
+#pragma unroll 1
+      for (int t = 1; t <= P; ++t)
+        jacobi_pair(t == 1 ? nullptr : buf[(P - t) % 2], b0, buf[(P - t + 1) % 2], wgt(1, 0), wgt(1, 2 * t - 1),
+                    wgt(1, 2 * t), t == P, fin);
+    }
+  }
+
+  // Lower end of the spectrum of D^-1 A for the Chebyshev interval, 0 when
+  // defect corrections are not for this operator.  From the diagonal's
+  // stiffness to mass ratio r at the nodes: on a uniform grid the Q1 mass matrix
+  // relative to its diagonal is smallest, 2^-d, on the mode that alternates
+  // along every axis, where the stiffness is 2^(2-d) of its diagonal whatever
+  // the anisotropy, so that D^-1 A there is 2^-d (1 + 4 r) / (1 + r) (r capped
+  // where another mode may be lower); the constant has (3/2)^d / (1 + r).  The
+  // smallest of both over the nodes, less 5%, lay 5-20% below the smallest
+  // eigenvalue on every workload's operators.
+  __device__ __forceinline__ double spectrum_low() const {
+    const double th = prm.theta;
+    const TI* __restrict__ di = dinv;
+    double pm = 0.0, qm = 0.0;  // largest mass and stiffness share of the diagonal
+    const int nb = nband();
+    for (int q = threadIdx.x; q < nb; q += BLOCK) {
+      const int idx = bidx(q);
+      const double s = th * kdiag0[idx] * double(di[idx]);
+      qm = fmax(qm, s);
+      pm = fmax(pm, 1.0 - s);
+    }
+    qm = tmax(qm);
+    pm = tmax(pm);
+    const double rc = fmin(fmax(0.0, 1.0 / pm - 1.0), 0.5);
+    const double d2 = (DIM == 3) ? 0.125 : 0.25, d3 = (DIM == 3) ? 3.375 : 2.25;
+    const double low = 0.95 * fmin(d2 * (1.0 + 4.0 * rc) / (1.0 + rc), d3 * (1.0 - qm));
+    return pm <= 1.0 && low > 0.0 ? low : 0.0;
+  }
+
+  // Chebyshev weights of the defect corrections into omega row 1; returns the
+  // degree.  Narrowing step 0 covers [low, lmax] with an error reduction of
+  // 1e-4: 1e-3, 5e-4, 2e-4 and 1e-4 need 4, 3-3.5, 3 and 3 corrections per slab
+  // there.  Each further step divides the ratio lmax / low by kChebNarrow: where
+  // the solution is smooth the modes below the interval are hardly there, and
+  // fewer sweeps reduce the rest as far.  A level with its own sweep count or
+  // ratio keeps those.  Between two workgroup barriers.
+  __device__ __forceinline__ int cheb_interval(double low, double lmax, int step) const {
+    double ratio = lmax / low;
+    for (int i = 0; i < step; ++i) ratio /= kChebNarrow;
+    if (L->own_ratio > 0.0) ratio = L->own_ratio;
+    const double rt = sqrt(ratio), rho = (rt - 1.0) / (rt + 1.0);
+    int nc = L->own_sweeps;
+    if (nc <= 0) nc = (int)ceil(log(2.0 / (step ? 2.0 * kChebReduction : kChebReduction)) / -log(rho));
+    nc = min(max(nc, 3), kMaxSweeps);
+    if (nc % 2 != (DIM == 2 ? 1 : 0)) nc = nc < kMaxSweeps ? nc + 1 : nc - 1;  // 2D odd, 3D even
+    nc = __builtin_amdgcn_readfirstlane(nc);
+    __syncthreads();
+    if (threadIdx.x == 0) chebyshev_weights(lmax / ratio, lmax, nc, omega + kMaxSweeps);
+    __syncthreads();
+    return nc;
+  }
+  __device__ __forceinline__ int cheb_steps(double low, double lmax) const {  // narrowing steps down to a ratio of 3
+    if (L->own_ratio > 0.0 || L->own_sweeps > 0) return 0;
+    int g = 0;
+    for (double r = lmax / low / kChebNarrow; r > 3.0 && g < 8; r /= kChebNarrow) ++g;
+    return __builtin_amdgcn_readfirstlane(g);
+  }
+
   // lmax of D^-1 A_l by power iteration.
   // Uses buffers x0, x1 of grid l.  Returns the estimate (team-uniform).
   __device__ __forceinline__ double power_lmax(int l, TI* x0, TI* x1) const {
@@ -1427,44 +1575,33 @@ struct Team {
     }
     sync();
     double lam = 0.0;
+    TI scl = TI(1);
     const TI* __restrict__ w = mgW(l);
     const TI* __restrict__ di = mgI(l);
+    // the iterate is scaled to norm 1 by the pass that reads it next
     for (int it = 0; it < prm.power_iters; ++it) {
       double nn[2] = {0.0, 0.0};
       staged<TI>(
           l, x0, w, di, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
           [](TI a, TI ww) { return ww * a; },
           [&](int idx, int, int, int, TI ax, TI xown, TI, TI dio, TI) {
-            const TI y = ax * dio;
+            const TI y = ax * dio * scl, xs = xown * scl;
             gmem(x1)[idx] = y;
             nn[0] += double(y) * double(y);
-            nn[1] += double(xown) * double(xown);
-          });
+            nn[1] += double(xs) * double(xs);
+          },
+          false);
       tsum<2>(nn);
       lam = sqrt(nn[0] / nn[1]);
-      const TI scl = TI(1.0 / sqrt(nn[0]));
-      for (int q = threadIdx.x; q < nb; q += BLOCK) {
-        const int idx = l == 0 ? bidx(q) : q;
-        x0[idx] = x1[idx] * scl;
-      }
-      sync();
+      scl = TI(1.0 / sqrt(nn[0]));
+      TI* t = x0;
+      x0 = x1;
+      x1 = t;
     }
     bytes = uni(bytes + (prm.power_iters * (5.0 * sizeof(TI) * g.n + dbytes(l))));
     return lam;
   }
 };
-
-// Weights 1 / xi_s, xi_s the roots of the degree-K Chebyshev polynomial
-// shifted to [a, b], ordered to alternate large and small roots.
-__device__ inline void chebyshev_weights(double a, double b, int K, double* w) {
-  const double th = 0.5 * (b + a), de = 0.5 * (b - a);
-  const double PI = 3.14159265358979323846;
-  for (int s = 0; s < K; ++s) {
-    const int r = (s % 2 == 0) ? s / 2 : K - 1 - s / 2;
-    const double xi = th + de * cos(PI * (2 * r + 1) / (2.0 * K));
-    w[s] = 1.0 / xi;
-  }
-}
 
 template <typename TI, int DIM, int BLOCK, bool MG>
 __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restrict__ levels,
@@ -1533,6 +1670,13 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
 
   bool have_prev = false;
   const double* prevU = nullptr;
+  // Interval of the defect corrections, narrowing step `step`: every `wait`
+  // slabs one slab tries a narrower one and keeps it when it took less.  Trials
+  // go `jump` steps, one and three in turn while they fail (with fewer sweeps
+  // a step may need one correction more and the third step none); after each
+  // such pair the time to the next one doubles.
+  int step = 0, jump = 1, wait = 3, backoff = 8;
+  int slab_cost = 0;
 
   for (int it_s = 0; it_s < task.count; ++it_s) {
     const int s = task.order ? task.order[task.first + it_s * task.stride] : task.first + it_s * task.stride;
@@ -1566,6 +1710,13 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
     const double krylov_words = 7.0 + L->pc_words;
     double worst_final = 0.0;
     bool weights_ready = (prm.smoother == 0);
+    // defect correction by Chebyshev sweeps (the default way to a Newton step
+    // on single-grid levels): its degree (0: not used on this sample) and how
+    // many slabs in a row have had to fall back on GMRES
+    int nc = 0, fallbacks = 0;
+    double lmax0 = 0.0, low0 = 0.0;
+    int ngrow = 0;   // narrowing steps there are
+    if (wait < 2) wait = 2;
 
     for (int k = 0; k < m; ++k) {
       // ---- initial iterate of slab k ----
@@ -1590,13 +1741,24 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       // damping: the residual 2-norm of the last accepted iterate and the
       // fraction of the last Newton step in u (halved while the residual grows)
       double beta_acc = 0.0, tstep = 1.0;
-      for (; it < prm.newton_max; ++it) {
+      bool cheb = nc > 0;
+      int ncor = 0;  // defect corrections of the slab (not counted against newton_max)
+      int cost = 0;
+      bool wide = false;  // the slab has gone back to the whole interval
+      const bool trial = cheb && step + jump <= ngrow && --wait <= 0;
+      if constexpr (!MG) {
+        if (trial) nc = tm.cheb_interval(low0, lmax0, step + jump);
+      }
+      for (; it - ncor < prm.newton_max; ++it) {
         // ---- residual (float64) -> V_0, Jacobian weights on every grid ----
         TI* V0 = tm.V;
         TI* w0 = tm.mgW(0);
         double rr[1] = {0.0};
         STM_T0(t_res);
-        tm.bytes = uni(tm.bytes + (24.0 * n0 + 8.0 * g0.ne + 3.0 * sizeof(TI) * n0));
+        // 3D defect corrections start with the sweep from zero, om r / diag, here
+        TI* x1 = (DIM == 3 && !MG && cheb) ? tm.mgT(0) : nullptr;
+        const TI om1 = x1 ? tm.wgt(1, 0) : TI(0);
+        tm.bytes = uni(tm.bytes + (24.0 * n0 + 8.0 * g0.ne + (x1 ? 4.0 : 3.0) * sizeof(TI) * n0));
         for (int l = 1; l < L->nmg; ++l) tm.bytes = uni(tm.bytes + ((8.0 + sizeof(TI)) * L->g[l].n));
         {
           TI* __restrict__ di = tm.dinv;
@@ -1608,11 +1770,16 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
               [&](int idx, int i, int j, int k, double y, double uown, double, double kd, double) {
                 const double r = -y;
                 const double w = inv_dt - react_d(uown, kr, ar);
+                const TI dd = TI(1.0 / (th * kd + tm.nel(0, i, j, k) * cmd * w));
                 gmem(V0)[idx] = TI(r);
                 gmem(w0)[idx] = TI(w);
-                gmem(di)[idx] = TI(1.0 / (th * kd + tm.nel(0, i, j, k) * cmd * w));
+                gmem(di)[idx] = dd;
+                if constexpr (DIM == 3 && !MG) {
+                  if (x1) gmem(x1)[idx] = om1 * TI(r) * dd;
+                }
                 rr[0] += r * r;
-              });
+              },
+              false);
         }
         tm.coarse_weights(u, inv_dt);
         tm.template tsum<1>(rr);  // its barriers also publish the writes above
@@ -1627,6 +1794,33 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
           conv = true;
           dmax = 0.0;
           break;
+        }
+        // a defect correction that did not contract the residual well (the
+        // first one may owe its remainder to the reaction) leaves the rest of
+        // the slab to GMRES; one that made it grow is taken back
+        if (cheb && ncor > 0 && !(beta <= (ncor == 1 ? 0.5 : kContract) * beta_acc)) {
+          if constexpr (!MG) {
+            if (beta <= beta_acc && !wide && step + trial > 0) {  // first the whole interval
+              wide = true;
+              nc = tm.cheb_interval(low0, lmax0, 0);
+              x1 = nullptr;
+            } else {
+              cheb = false;
+              if (++fallbacks > kMaxFallbacks) nc = 0;
+            }
+          }
+          if (!(beta <= beta_acc)) {
+            for (int q = tid; q < nb; q += BLOCK) {
+              const int idx = tm.bidx(q);
+              u[idx] = isfinite(beta) ? u[idx] - double(tm.Z[idx]) : uprev[idx];
+            }
+            tm.bytes = uni(tm.bytes + (16.0 + sizeof(TI)) * n0);
+            beta_acc = HUGE_VAL;
+            dprev = 0.0;
+            ++ncor;
+            tm.sync();
+            continue;
+          }
         }
         // the last step made the residual grow (or not finite): take half of
         // it back, u -= (t/2) delta, and evaluate again (Armijo-style halving
@@ -1651,11 +1845,74 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             TI* x0 = (l == 0) ? tm.V + vs : tm.mgX(l);
             TI* x1 = (l == 0) ? tm.V + 2 * vs : tm.mgT(l);
             const double lmax = 1.05 * tm.power_lmax(l, x0, x1);
+            if (l == 0) lmax0 = uni(lmax);
             const int K = (l == L->nmg - 1) ? L->sweeps : prm.smooth_steps;
             if (tid == 0) chebyshev_weights(lmax / L->cheb_ratio, lmax, K, omega_tab + l * kMaxSweeps);
           }
+          if constexpr (!MG) {
+            low0 = uni(tm.spectrum_low());
+            if (low0 > 0.0 && lmax0 > low0 && lmax0 < 100.0 * low0) {
+              ngrow = tm.cheb_steps(low0, lmax0);
+              step = min(step, ngrow);
+              nc = tm.cheb_interval(low0, lmax0, step);
+              cheb = true;
+            }
+          }
           __syncthreads();
           weights_ready = true;
+        }
+
+        if constexpr (!MG) {
+          if (cheb) {
+            // ---- defect correction: u += P(A) r, P the Chebyshev sweeps ----
+            model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * 5.0 * nc);
+            STM_T0(t_ch);
+            double dm = 0.0;
+            tm.bytes = uni(tm.bytes + 16.0 * n0);
+            tm.chebyshev(V0, tm.Z, nc, x1 != nullptr, [&](int idx, TI xn) {
+              const double dl = double(xn);
+              gmem(u)[idx] += dl;
+              dm = fmax(dm, fabs(dl));
+            });
+            dmax = uni(tm.tmax(dm));  // its barrier also publishes u to the other members
+            STM_T1(t_ch, 1);
+            ++krylov_total;
+            ++ncor;
+            cost += nc + kCorrectionCost;
+            if (!(dmax < 1e3)) {  // far out of range or not finite: GMRES from the previous slab's state
+              for (int q = tid; q < nb; q += BLOCK) {
+                const int idx = tm.bidx(q);
+                u[idx] = uprev[idx];
+              }
+              nc = 0;
+              cheb = false;
+              beta_acc = HUGE_VAL;
+              dprev = 0.0;
+              tm.sync();
+              continue;
+            }
+            if (dmax <= prm.newton_tol) {
+              conv = true;
+              ++it;
+              break;
+            }
+            // Corrections contract linearly: the next one, which is also the
+            // error left, is about dmax times the last contraction.  The bound
+            // is stricter than for the Newton steps below, which mostly end far
+            // below their estimate.
+            if (it >= 1) {
+              const double ratio = dmax / dprev;
+              if (ratio < 0.5 && dmax * fmax(ratio, kChebReduction) <= kChebTol * prm.newton_tol) {
+                conv = true;
+                ++it;
+                break;
+              }
+            }
+            dprev = uni(dmax);
+            eta = uni(fmax(prm.gmres_rtol, fmin(1e-4, 0.01 * dmax)));
+            if (ncor >= kMaxCorrections) cheb = false;
+            continue;
+          }
         }
 
         // ---- GMRES(restart), right-preconditioned by the V-cycle ----
@@ -1939,6 +2196,36 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       }
       if (status == -5) break;
       if (!conv && status == 0) status = -4;
+      if constexpr (!MG) {
+        if (cheb) {
+          fallbacks = 0;
+          if (trial) {
+            const bool better = !wide && 32 * cost < 31 * slab_cost;
+            if (better) {
+              step += jump;
+              slab_cost = cost;
+              wait = 1;
+              backoff = 8;
+            } else {
+              nc = tm.cheb_interval(low0, lmax0, step);
+              wait = jump == 1 ? 2 : backoff;
+              if (jump > 1) backoff = min(2 * backoff, 64);
+              jump = jump == 1 ? 3 : 1;
+            }
+            if (step + jump > ngrow) jump = 1;
+          } else {
+            if (step > 0 && (wide || 8 * cost > 9 * slab_cost)) {  // the solution has changed: one step back
+              step -= 1;
+              wait = backoff;
+              nc = tm.cheb_interval(low0, lmax0, step);
+            }
+            slab_cost = cost;
+          }
+        } else if (nc > 0) {
+          step = 0;
+          nc = tm.cheb_interval(low0, lmax0, 0);
+        }
+      }
       newton_total += it;
       newton_max_slab = max(newton_max_slab, it);
       worst_final = uni(fmax(worst_final, dmax));
@@ -2409,21 +2696,28 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
 }
 
 // ---------------------------------------------------------------------------
-// host launcher
+// Kernels of one dimension and inner precision: this file is compiled once for
+// each pair (STM_SOLVER_DIM 2 or 3, STM_SOLVER_FP32 0 or 1), side by side.
 // ---------------------------------------------------------------------------
-template <typename TI, int DIM, bool MG>
+#if STM_SOLVER_FP32
+using SolverInner = float;
+#else
+using SolverInner = double;
+#endif
+
+template <bool MG>
 static const void* kernel_for_block(int block, bool global) {
   if (global) {
     switch (block) {
-      case 256: return (const void*)st_global_kernel<TI, DIM, 256, MG>;
-      case 512: return (const void*)st_global_kernel<TI, DIM, 512, MG>;
+      case 256: return (const void*)st_global_kernel<SolverInner, STM_SOLVER_DIM, 256, MG>;
+      case 512: return (const void*)st_global_kernel<SolverInner, STM_SOLVER_DIM, 512, MG>;
       default: return nullptr;
     }
   }
   switch (block) {
-    case 256: return (const void*)st_team_kernel<TI, DIM, 256, MG>;
-    case 512: return (const void*)st_team_kernel<TI, DIM, 512, MG>;
-    case 1024: return (const void*)st_team_kernel<TI, DIM, 1024, MG>;
+    case 256: return (const void*)st_team_kernel<SolverInner, STM_SOLVER_DIM, 256, MG>;
+    case 512: return (const void*)st_team_kernel<SolverInner, STM_SOLVER_DIM, 512, MG>;
+    case 1024: return (const void*)st_team_kernel<SolverInner, STM_SOLVER_DIM, 1024, MG>;
     default: return nullptr;
   }
 }
@@ -2431,38 +2725,9 @@ static const void* kernel_for_block(int block, bool global) {
 // The multi-grid kernel variant (MG = true) serves launches with a level
 // whose V-cycle has coarse grids; the others take the single-grid variant,
 // which compiles none of the coarse-grid code.
-template <int DIM>
-static const void* kernel_for_dim(bool fp32, bool mg, int block, bool global) {
-  if (mg)
-    return fp32 ? kernel_for_block<float, DIM, true>(block, global) : kernel_for_block<double, DIM, true>(block, global);
-  return fp32 ? kernel_for_block<float, DIM, false>(block, global) : kernel_for_block<double, DIM, false>(block, global);
-}
-
-static const void* solver_kernel(int dim, bool fp32, bool mg, int block, bool global) {
-  return dim == 2 ? kernel_for_dim<2>(fp32, mg, block, global) : kernel_for_dim<3>(fp32, mg, block, global);
-}
-
-hipError_t launch_team_solver(int dim, bool inner_fp32, bool mg, const LevelDev* levels, const TeamTask* tasks,
-                              int n_blocks, SolverParams prm, int block, size_t lds_bytes, bool cooperative,
-                              hipStream_t st) {
-  if (n_blocks <= 0) return hipSuccess;
-  const void* f = solver_kernel(dim, inner_fp32, mg, block, prm.global_st != 0);
-  if (!f) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-  if (e != hipSuccess) return e;
-  void* args[] = {(void*)&levels, (void*)&tasks, (void*)&prm};
-  if (cooperative) return hipLaunchCooperativeKernel(f, dim3(n_blocks), dim3(block), args, (unsigned)lds_bytes, st);
-  return hipLaunchKernel(f, dim3(n_blocks), dim3(block), args, lds_bytes, st);
-}
-
-// Co-resident workgroups per CU for a launch configuration (0 on error).
-int team_solver_occupancy(int dim, bool inner_fp32, bool mg, bool global, int block, size_t lds_bytes) {
-  int nb = 0;
-  const void* f = solver_kernel(dim, inner_fp32, mg, block, global);
-  if (!f) return 0;
-  if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, block, lds_bytes) != hipSuccess) return 0;
-  return nb;
+template <>
+const void* solver_kernel_of<STM_SOLVER_DIM, STM_SOLVER_FP32 != 0>(bool mg, int block, bool global) {
+  return mg ? kernel_for_block<true>(block, global) : kernel_for_block<false>(block, global);
 }
 
 }  // namespace stm

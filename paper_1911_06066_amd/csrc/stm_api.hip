@@ -252,6 +252,8 @@ stm_status build_level(stm_ctx* c, int l, LevelHost& out) {
   d.nmg = nmg;
   d.sweeps = lv.smooth_sweeps > 0 ? lv.smooth_sweeps : p.coarse_sweeps;
   d.cheb_ratio = lv.cheb_ratio > 0 ? lv.cheb_ratio : p.cheb_ratio;
+  d.own_sweeps = lv.smooth_sweeps;
+  d.own_ratio = lv.cheb_ratio;
 
   // fibre table of every grid, per element row (2D) / layer (3D) at that grid's centroids
   const GridDev& g0 = d.g[0];

@@ -44,6 +44,8 @@ struct LevelDev {
                                 // (per-step model: 5 per sweep and per residual, on each grid
                                 // weighted by its nodes)
   double cheb_ratio;            // Chebyshev interval ratio of the sweep weights
+  int own_sweeps;               // degree and interval ratio of the defect corrections where the level
+  double own_ratio;             // gives its own, else 0 (both from the operator's spectrum)
   GridDev g[kMaxMG];
   const double* fib[kMaxMG];    // fibre table of every grid: per element row (2D) / layer (3D): c^2, s^2, c s
                                 // at that grid's own element centroids

@@ -16,6 +16,14 @@ namespace stm {
 hipError_t launch_team_solver(int dim, bool inner_fp32, bool mg, const LevelDev* levels, const TeamTask* tasks,
                               int n_blocks, SolverParams prm, int block, size_t lds_bytes, bool cooperative,
                               hipStream_t st);
+// The solver kernel of a dimension and inner precision (st_solver.hip; one
+// translation unit each), null where there is none for the block size.
+template <int DIM, bool FP32>
+const void* solver_kernel_of(bool mg, int block, bool global);
+template <> const void* solver_kernel_of<2, false>(bool mg, int block, bool global);
+template <> const void* solver_kernel_of<2, true>(bool mg, int block, bool global);
+template <> const void* solver_kernel_of<3, false>(bool mg, int block, bool global);
+template <> const void* solver_kernel_of<3, true>(bool mg, int block, bool global);
 // Co-resident solver workgroups per CU for a configuration (0 on error);
 // global: the global space-time kernel (SolverParams::global_st).
 int team_solver_occupancy(int dim, bool inner_fp32, bool mg, bool global, int block, size_t lds_bytes);
