@@ -179,85 +179,56 @@ __device__ __forceinline__ void elem_apply_2d(const T (&k)[4], const T (&m)[4], 
   out[3] = p1 + q1 + A + B + cm * (T(2) * r11 + r01);
 }
 
-// The 3D element: with vertex v = bx + 2 by + 4 bz and s = 2 b - 1 per axis,
-//   (K_e k)_v = s_x A(by, bz) + s_y B(bx, bz) + s_z C(bx, by)
-//   A = ax [M_y M_z dx] + axy [M_z hy],  B = ay [M_x M_z dy] + axy [M_z hx],
-//   C = az [M_x M_y dz],
-//   (M_e m)_v = cm [M_x M_y M_z m]_v
-// where dx(by, bz) are the four x-edge differences of k (likewise dy, dz),
-// hx(bz), hy(bz) the sums of a z-layer's two x- resp. y-edge differences, and
-// M = [[2, 1], [1, 2]] along the named axis; ax = D_xx h_y h_z / (36 h_x),
-// ay, az likewise, axy = D_xy h_z / 24, cm = h_x h_y h_z / 216 (an element
-// with a constant tensor whose fibres lie in the x-y plane).  Only the unique
-// factors are formed, which keeps few values live.
+// The 3D element in the basis of sums and differences: per axis a vertex pair
+// (v0, v1) becomes s = v0 + v1, d = v1 - v0.  There the 1D mass factor
+// [[2, 1], [1, 2]] is diag(3, 1), the stiffness factor [[1, -1], [-1, 1]] is
+// diag(0, 2), and the mixed one takes s to d.  With m(abc) = 3^(number of s)
+// over the three axes and ax = D_xx h_y h_z / (36 h_x), ay, az likewise,
+// axy = D_xy h_z / 24 and cm = h_x h_y h_z / 216 (a constant tensor whose fibres
+// lie in the x-y plane), K_e k + M_e mv is
+//   d..: 2 ax m / 3^[..] k(d..) + 4 axy 3^[z = s] k(sd.) (for ds.), y and z likewise,
+//   plus cm m mv,
+// and the way back to the vertices takes 1/2 per axis.  An x-y face is
+// transformed once for the two layers it bounds; a layer needs the sums and
+// differences of its two faces, 11 products for the stiffness and 8 for the mass.
 template <typename T>
-__device__ __forceinline__ void m1_pair(T& a, T& b) {
-  const T x = a, y = b;
-  a = T(2) * x + y;
-  b = x + T(2) * y;
+__device__ __forceinline__ void face_transform(const T (&v)[4], T (&h)[4]) {
+  const T s0 = v[0] + v[1], d0 = v[1] - v[0], s1 = v[2] + v[3], d1 = v[3] - v[2];
+  h[0] = s0 + s1;  // ss
+  h[1] = d0 + d1;  // ds
+  h[2] = s1 - s0;  // sd
+  h[3] = d1 - d0;  // dd
 }
 
+// One element layer between its bottom face (kb, mb) and top face (kt, mt), all
+// transformed in x and y.  gx = 3/4 ax (gy, gz likewise), gxy = axy / 2,
+// c1 = cm / 8, c3 = 3 c1, c9 = 9 c1.  bottom: carry plus the layer's
+// contribution to the lower plane; carry: its contribution to the upper plane.
 template <typename T>
-__device__ __forceinline__ void elem_apply_3d(const T (&k)[8], const T (&m)[8], T ax, T ay, T az, T axy, T cm,
-                                              T (&out)[8]) {
-  // edge differences: index (the two other axes' bits) = first + 2 second
-  T dx[4], dy[4], dz[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int b1 = u & 1, b2 = u >> 1;
-    dx[u] = k[1 + 2 * b1 + 4 * b2] - k[2 * b1 + 4 * b2];  // (by, bz)
-    dy[u] = k[b1 + 2 + 4 * b2] - k[b1 + 4 * b2];          // (bx, bz)
-    dz[u] = k[b1 + 2 * b2 + 4] - k[b1 + 2 * b2];          // (bx, by)
-  }
-  T hx[2] = {dx[0] + dx[1], dx[2] + dx[3]};  // per bz
-  T hy[2] = {dy[0] + dy[1], dy[2] + dy[3]};
-  m1_pair(hx[0], hx[1]);
-  m1_pair(hy[0], hy[1]);
-  // M along both other axes of each difference set
-  m1_pair(dx[0], dx[1]);
-  m1_pair(dx[2], dx[3]);
-  m1_pair(dx[0], dx[2]);
-  m1_pair(dx[1], dx[3]);
-  m1_pair(dy[0], dy[1]);
-  m1_pair(dy[2], dy[3]);
-  m1_pair(dy[0], dy[2]);
-  m1_pair(dy[1], dy[3]);
-  m1_pair(dz[0], dz[1]);
-  m1_pair(dz[2], dz[3]);
-  m1_pair(dz[0], dz[2]);
-  m1_pair(dz[1], dz[3]);
-  T fm[8];
-#pragma unroll
-  for (int v = 0; v < 8; ++v) fm[v] = m[v];
-#pragma unroll
-  for (int v = 0; v < 8; v += 2) m1_pair(fm[v], fm[v + 1]);
-#pragma unroll
-  for (int v = 0; v < 8; ++v)
-    if (!(v & 2)) m1_pair(fm[v], fm[v + 2]);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) m1_pair(fm[v], fm[v + 4]);
-  T A[4], B[4], C[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    A[u] = ax * dx[u] + axy * hy[u >> 1];
-    B[u] = ay * dy[u] + axy * hx[u >> 1];
-    C[u] = az * dz[u];
-  }
-#pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    const int bx = v & 1, by = (v >> 1) & 1, bz = v >> 2;
-    const T a = A[by + 2 * bz], b = B[bx + 2 * bz], c = C[bx + 2 * by];
-    T acc = bx ? a : -a;
-    acc += by ? b : -b;
-    acc += bz ? c : -c;
-    out[v] = acc + cm * fm[v];
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void elem_apply_3d(const T (&k)[8], const T (&m)[8], const Tensor3<T>& D, T cxx, T cyy,
-                                              T czz, T cxy, T cm, T (&out)[8]) {
-  elem_apply_3d<T>(k, m, D.xx * cxx, D.yy * cyy, D.zz * czz, D.xy * cxy, cm, out);
+__device__ __forceinline__ void layer_apply(const T (&kb)[4], const T (&kt)[4], const T (&mb)[4], const T (&mt)[4],
+                                            T gx, T gy, T gz, T gxy, T c1, T c3, T c9, T (&carry)[4],
+                                            T (&bottom)[4]) {
+  const T k1s = kb[1] + kt[1], k2s = kb[2] + kt[2], k3s = kb[3] + kt[3];
+  const T k0d = kt[0] - kb[0], k1d = kt[1] - kb[1], k2d = kt[2] - kb[2], k3d = kt[3] - kb[3];
+  const T third = T(1) / T(3);
+  const T gxz = gx + gz, gyz = gy + gz, gs = gx + gy;
+  // a third of the z-sum's part, and the z-difference's part
+  const T s0 = c9 * (mb[0] + mt[0]);
+  const T s1 = fma(gx, k1s, fma(gxy, k2s, c3 * (mb[1] + mt[1])));
+  const T s2 = fma(gy, k2s, fma(gxy, k1s, c3 * (mb[2] + mt[2])));
+  const T s3 = fma(gs * third, k3s, c1 * (mb[3] + mt[3]));
+  const T d0 = fma(T(3) * gz, k0d, c9 * (mt[0] - mb[0]));
+  const T d1 = fma(gxz, k1d, fma(gxy, k2d, c3 * (mt[1] - mb[1])));
+  const T d2 = fma(gyz, k2d, fma(gxy, k1d, c3 * (mt[2] - mb[2])));
+  const T d3 = fma((gs + gz) * third, k3d, c1 * (mt[3] - mb[3]));
+  bottom[0] = fma(T(3), s0, carry[0]) - d0;
+  bottom[1] = fma(T(3), s1, carry[1]) - d1;
+  bottom[2] = fma(T(3), s2, carry[2]) - d2;
+  bottom[3] = fma(T(3), s3, carry[3]) - d3;
+  carry[0] = fma(T(3), s0, d0);
+  carry[1] = fma(T(3), s1, d1);
+  carry[2] = fma(T(3), s2, d2);
+  carry[3] = fma(T(3), s3, d3);
 }
 
 }  // namespace stm

@@ -46,6 +46,15 @@
 
 namespace stm {
 
+// A node as a pass hands it to its body: a uniform base and the thread's number
+// from there, which together are the node's index.  node_ref forms the address
+// from a uniform pointer and a 32-bit offset.
+struct NodeAt {
+  int base;
+  unsigned q;
+  __device__ __forceinline__ operator int() const { return base + (int)q; }
+};
+
 // Optional per-phase timers (development builds with -DSTM_PHASE_TIMERS):
 // thread 0 accumulates wall-clock ticks of each solver phase.
 #ifdef STM_PHASE_TIMERS
@@ -91,6 +100,21 @@ __device__ __forceinline__ const STM_CONST T* cmem(const T* p) {
   return (const STM_CONST T*)p;
 }
 
+template <typename T>
+__device__ __forceinline__ STM_GLOBAL T& node_ref(T* p, NodeAt at) {
+  return gmem(p + at.base)[at.q];
+}
+
+// A uniform pointer as of here: what a pass derives from it is not computed
+// ahead of the loops around the pass.  Without this every pass's tile sizes and
+// addresses stay live over the whole solve, and their spills (SGPRs to VGPR
+// lanes, 60-100 v_readlane per z-step) cost the passes.
+template <typename P>
+__device__ __forceinline__ P* here(P* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // The stiffness argument c * v of a pass (kval(v, .) = c v).  The 3D pass
 // folds c into the element's conductivity factors instead of scaling the
 // eight vertex values; for c a power of two (the theta of backward Euler and
@@ -119,6 +143,8 @@ struct SigmaOf<float> {
   using type = float;
 };
 
+constexpr int kWaitVm = 0x0f70;       // s_waitcnt operand: vector memory operations only
+constexpr int kDeviceScope = 16;       // cache policy of a load: device scope (sc1)
 constexpr int kPartStride = 16;       // doubles per member in the partials buffer
 constexpr double kMinStep = 1.0 / 64;  // smallest damped fraction of a Newton step
 constexpr unsigned kSpinLimit = 1u << 25;
@@ -208,6 +234,18 @@ __device__ inline void chebyshev_weights(double a, double b, int K, double* w) {
   }
 }
 
+// What the steps of a solve take and give (dmax and resid also carry the two ends
+// of the spectrum).
+struct StepIO {
+  double *u, *uprev, *dlt;
+  double beta, eta, krylov_words;
+  double model_bytes;
+  double dmax;         // max-norm of the step
+  double resid;        // residual norm reached (residual step: its square)
+  int jdim;            // Krylov iterations
+  int x1, nc;          // the correction's first sweep is the residual step's; its sweeps
+};
+
 // MG: the launch contains a level with a multigrid hierarchy.  Without one the
 // V-cycle is the Chebyshev-weighted sweeps on the level's grid and no
 // coarse-grid code is compiled into the kernel (it would cost registers).
@@ -233,6 +271,8 @@ struct Team {
   double* part;
   int* fault;
   mutable unsigned gen;  // barriers passed
+  mutable unsigned hgen;  // halo barriers passed
+  int gy, gz;            // the team's members along y and z (rank = iy gz + iz)
   mutable unsigned rslot;  // reductions done (partials double buffer)
   mutable bool broken;   // a barrier wait timed out: stop waiting
   // Algorithmic bytes of the passes run so far: every array a pass reads or
@@ -303,6 +343,51 @@ struct Team {
       __syncthreads();
     }
   }
+  // Barrier between two sweeps of a correction.  A sweep reads of the other
+  // members only the adjacent ones' boundary values of x, and x is exchanged
+  // past the caches: stored and loaded with agent-scope accesses (coh_store,
+  // the coherent loads of the passes), which need no write-back and no
+  // invalidation.  So every member waits for its neighbours' flags only, the L2
+  // keeps the fields that a sweep only reads, and a member that is late delays
+  // its neighbours and not the team.  A neighbour's flag also says that it has
+  // read what the member overwrites next.
+  __device__ __forceinline__ unsigned* halo_flag(int r) const {
+    return reinterpret_cast<unsigned*>(part + r * kPartStride + kPartStride - 1);  // a word the partials leave free
+  }
+  __device__ __forceinline__ void halo_barrier() const {
+    if (G == 1) {
+      __syncthreads();
+      return;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    hgen += 1;
+    if (threadIdx.x < kWave) {
+      const int lane = threadIdx.x;
+      if (lane == 0) __hip_atomic_store(halo_flag(rank), hgen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int iy = rank / gz + lane / 3 - 1, iz = rank % gz + lane % 3 - 1;
+      const bool adjacent = lane < 9 && lane != 4 && iy >= 0 && iy < gy && iz >= 0 && iz < gz;
+      const unsigned* f = halo_flag(adjacent ? iy * gz + iz : rank);
+      unsigned spins = 0;
+      while (!broken) {
+        const bool there = !adjacent || (int)(__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - hgen) >= 0;
+        if (__all(there)) break;
+        __builtin_amdgcn_s_sleep(1);
+        if (++spins > kSpinLimit) {
+          broken = true;
+          if (lane == 0) __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // x of a sweep: past the caches when other members read it
+  __device__ __forceinline__ void coh_store(STM_GLOBAL TI* p, TI v) const {
+    if (G > 1)
+      __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      *p = v;
+  }
   // End of a pass whose results other members read.
   __device__ __forceinline__ void sync() const { team_barrier(); }
 
@@ -340,13 +425,14 @@ struct Team {
 
   // ---- owned nodes of grid 0 ----------------------------------------------
   // Rows per tile of a z-marching pass on grid l with fields of fbytes bytes:
-  // the LDS budget (set on the host) and the per-thread element, staged-node
-  // and output-node counts.
-  static constexpr int kCE = 3, kCN = 4, kCB = 3;
-  __device__ __forceinline__ int zrows_max(int l, int fbytes) const {
-    const GridDev& g = L->g[l];
-    return max(1, min((int)L->tile_y[l][fbytes == 8 ? 0 : 1][0],
-                      min(kCE * BLOCK / g.ex - 1, min(kCN * BLOCK / g.nx - 2, kCB * BLOCK / g.nx))));
+  // the LDS budget (set on the host) and the per-thread element and output-node
+  // columns.
+  static constexpr int kCE = BLOCK == 1024 ? 2 : 3, kCB = kCE;
+  template <typename LP>
+  __device__ __forceinline__ int zrows_max(LP Lp, int l, int fbytes) const {
+    const auto& g = Lp->g[l];
+    return max(1, min((int)Lp->tile_y[l][fbytes == 8 ? 0 : 1][0],
+                      min(kCE * BLOCK / g.ex - 1, kCB * BLOCK / g.nx)));
   }
   // A member owns node rows [jb0, jb1) of planes [kb0, kb1) (3D), q-th in
   // plane-major order.
@@ -373,15 +459,16 @@ struct Team {
     int Gz = 1;
     if constexpr (DIM == 3) {
       // Gz minimises the z-steps of a member's pass: tiles x (planes + the
-      // step on the layer below + about two steps of prologue), every member
-      // keeping at least 4 planes
-      const int Rmax = zrows_max(0, sizeof(TI));
+      // step on the layer below in every group but the first + about two steps
+      // of prologue), every member keeping at least 4 planes (less one where the
+      // groups' steps are evened out)
+      const int Rmax = zrows_max(L, 0, sizeof(TI));
       int best = -1;
       for (int d = 1; d <= G; ++d) {
         if (G % d != 0 || g.nz < 4 * d) continue;
         const int Gy = G / d;
-        const int rows = (g.ny + Gy - 1) / Gy, planes = (g.nz + d - 1) / d;
-        const int cost = ((rows + Rmax - 1) / Rmax) * (planes + (d > 1 ? 1 : 0) + 2);
+        const int rows = (g.ny + Gy - 1) / Gy, steps = (g.nz + d - 1 + d - 1) / d;
+        const int cost = ((rows + Rmax - 1) / Rmax) * (steps + 2);
         if (best < 0 || cost < best) {
           best = cost;
           Gz = d;
@@ -389,10 +476,14 @@ struct Team {
       }
     }
     const int Gy = G / Gz, ry = rank / Gz, rz = rank - ry * Gz;
+    gy = Gy;
+    gz = Gz;
     jb0 = (int)((long long)ry * g.ny / Gy);
     jb1 = (int)((long long)(ry + 1) * g.ny / Gy);
-    kb0 = (DIM == 3) ? (int)((long long)rz * g.nz / Gz) : 0;
-    kb1 = (DIM == 3) ? (int)((long long)(rz + 1) * g.nz / Gz) : 1;
+    // the groups share the z-steps evenly, nz planes and Gz - 1 steps below a group
+    const int steps = g.nz + Gz - 1;
+    kb0 = (DIM == 3) ? (int)((long long)rz * steps / Gz) - max(rz - 1, 0) : 0;
+    kb1 = (DIM == 3) ? (int)((long long)(rz + 1) * steps / Gz) - rz : 1;
   }
 
   // ---- staged pass on grid 0 ----------------------------------------------
@@ -409,13 +500,14 @@ struct Team {
   // Grid l >= 1 (a coarse V-cycle grid, one-workgroup teams) is staged the
   // same way, with its own conductivities, fibre rows and tiles, every row
   // owned.
-  // publish = false leaves the closing team barrier to the reduction that
-  // the caller starts right after the pass.
-  template <typename T, typename KV, typename MV, typename Body>
+  // NF: how many of f2, f3 there are.  publish = false leaves the closing team
+  // barrier to the reduction that the caller starts right after the pass.
+  // COH: f0 is read with agent-scope loads (3D; see halo_barrier).
+  template <typename T, int NF, bool COH = false, typename KV, typename MV, typename Body>
   __device__ __forceinline__ void staged(int l, const T* __restrict__ f0, const T* __restrict__ f1, const T* __restrict__ f2,
                          const T* __restrict__ f3, KV kval, MV mval, Body body, bool publish = true) const {
     if constexpr (DIM == 3) {
-      zmarch<T>(l, f0, f1, f2, f3, kval, mval, body);
+      zmarch<T, NF, COH>(l, f0, f1, f2, f3, kval, mval, body);
     } else {
       staged_tiles<T>(l, f0, f1, f2, f3, kval, mval, body);
     }
@@ -426,34 +518,34 @@ struct Team {
   // The owned rows of grid l are cut into y-tiles of Ry rows over the whole x
   // extent, and each tile marches through the owned planes [kb0, kb1), with
   // one step on the layer below kb0 first (its top-face contributions) when
-  // kb0 > 0.  LDS holds per thread the top-face contributions of its elements
-  // of the previous layer (element q always belongs to thread q % BLOCK; four
-  // values per element, read and written as one vector), a ring of three
-  // planes of f0, f1 over the tile's rows plus a one-row halo, four partial
+  // kb0 > 0.  A thread keeps up to kCE element columns (q = thread + n BLOCK)
+  // and kCB output columns for the whole march.  LDS holds a ring of three
+  // planes of f0, f1 over the tile's rows plus a one-row halo and four partial
   // sums per element of one element layer with a border of zeros (one element
-  // each side in x and y), and two slots of f2, f3 on the output rows and of
-  // the layer conductivities.  Step k:
-  //   * direct-to-LDS loads (no registers) of plane k+2 of f0, f1 into the
-  //     free ring slot, of the conductivities of layer k+1 and of f2, f3 on
-  //     plane k+1 into the other slots;
-  //   * phase A: the vertex contributions of the thread's elements of layer k
-  //     (between planes k and k+1) by sum factorisation; bottom-face ones plus
-  //     the stored top-face ones of layer k-1 are the four sums the element
-  //     gives plane k (to LDS); the new top-face ones replace the stored ones;
+  // each side in x and y).  Step k:
+  //   * loads to registers of the conductivities of layer k+1 and of f2, f3 on
+  //     plane k, direct-to-LDS loads of plane k+2 of f0, f1 into the free slot;
+  //   * phase A: the element operator of layer k in the basis of sums and
+  //     differences along each axis, where mass is diagonal and stiffness
+  //     nearly (q1_stencil.h).  The x-y transform of a face is formed once and
+  //     kept in registers for the layer above, as is the layer's top half; its
+  //     bottom half plus the kept one of layer k-1, transformed back, are the
+  //     four sums the element gives plane k (to LDS);
   //   * an LDS-only barrier (the loads stay in flight);
   //   * phase B: every output node of plane k adds the sums of the four
   //     elements around it in its plane (the zero border stands for elements
   //     outside the grid) and calls body;
-  //   * a workgroup barrier, which also waits for the step's loads.
+  //   * a wait for the step's loads before the first store of body, and an
+  //     LDS-only barrier at the end (the stores stay in flight).
   // f0 and f1 are read from memory once per tile (plus the halo rows), f2, f3
   // and the conductivities once.  A stiffness argument kval = KScale{c} is
   // folded into the element factors.
-  template <typename T, typename KV, typename MV, typename Body>
+  template <typename T, int NF, bool COH, typename KV, typename MV, typename Body>
   __device__ __forceinline__ void zmarch(int l, const T* __restrict__ f0, const T* __restrict__ f1,
                                          const T* __restrict__ f2, const T* __restrict__ f3, KV kval, MV mval,
                                          Body body) const {
-    using T4 = T __attribute__((ext_vector_type(4)));
-    const GridDev& g = L->g[l];
+    const STM_CONST LevelDev* __restrict__ Lp = cmem(here(L));
+    const STM_CONST GridDev& g = Lp->g[l];
     const int nx = g.nx, ny = g.ny, nz = g.nz, EX = g.ex, EY = g.ey, EZ = g.ez;
     const unsigned mnx = g.mnx, mex = g.mex;
     const int plane = ny * nx, eplane = EY * EX;
@@ -462,14 +554,13 @@ struct Team {
     const int jb0 = l == 0 ? this->jb0 : 0, jb1 = l == 0 ? this->jb1 : ny;
     const int kb0 = l == 0 ? this->kb0 : 0, kb1 = l == 0 ? this->kb1 : nz;
     const int ks = max(kb0 - 1, 0);  // first step: the layer below the first owned plane
-    const int Rmax = zrows_max(l, sizeof(T));
+    const int Rmax = zrows_max(Lp, l, sizeof(T));
     // as few tiles as Rmax allows, of equal height
     const int ntl = (jb1 - jb0 + Rmax - 1) / Rmax;
     const int Ry = (jb1 - jb0 + ntl - 1) / max(ntl, 1);
     using TS = typename SigmaOf<T>::type;
-    constexpr int WS = sizeof(TS) / 4;  // dwords per conductivity
     const STM_GLOBAL TS* __restrict__ sg = gmem(mgST<T>(l));
-    const STM_CONST double* __restrict__ fib = cmem(L->fib[l]);
+    const STM_CONST double* __restrict__ fib = cmem(Lp->fib[l]);
     const STM_GLOBAL T* __restrict__ g0 = gmem(f0);
     const STM_GLOBAL T* __restrict__ g1 = gmem(f1);
     const STM_GLOBAL T* __restrict__ g2 = gmem(f2);
@@ -479,10 +570,13 @@ struct Team {
     // the stiffness scale of a KScale argument goes into the element factors
     T ksc = T(1);
     if constexpr (IsKScale<KV>::value) ksc = kval.c;
-    const T cxx = ksc * (hy * hz / (T(36) * hx)), cyy = ksc * (hx * hz / (T(36) * hy));
-    const T czz = ksc * (hx * hy / (T(36) * hz)), cxy = ksc * (hz / T(24));
-    const T cm = hx * hy * hz / T(216);
+    const T cxx = ksc * (hy * hz / (T(48) * hx)), cyy = ksc * (hx * hz / (T(48) * hy));
+    const T czz = ksc * (hx * hy / (T(48) * hz)), cxy = ksc * (hz / T(48));
+    const T kz1 = T(zr) * czz, kz0 = T(tau) * czz, tauT = T(tau);
+    const T c1 = hx * hy * hz / T(1728), c3 = T(3) * c1, c9 = T(9) * c1;
     const int tid = threadIdx.x;
+    // the wave's first thread: a wave without an n-th column skips it
+    const int wfirst = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
     constexpr int WT = sizeof(T) / 4;  // dwords per value
     for (int j0 = jb0; j0 < jb1; j0 += Ry) {
       const int je = min(j0 + Ry, jb1);          // output rows [j0, je)
@@ -490,165 +584,218 @@ struct Team {
       const int jr1 = min(je, ny - 1);
       const int ey1 = min(je - 1, EY - 1);       // element rows [jr0, ey1]
       const int lay = (jr1 - jr0 + 1) * nx;      // staged nodes per plane
-      const int elay = (ey1 - jr0 + 1) * EX;     // elements per layer
-      const int slay = (ey1 - jr0 + 3) * EXP;    // padded sums per vertex slot
+      const int layp = (lay + 3) & ~3;           // slots of whole 16-byte words
+      const int erows = ey1 - jr0 + 1;
+      const int elay = erows * EX;               // elements per layer
+      const int slay = (erows + 2) * EXP;        // padded sums per vertex slot
       const int nc = (je - j0) * nx;             // output nodes per plane
       const int gn0 = jr0 * nx, ge0 = jr0 * EX, go0 = j0 * nx;
-      T4* __restrict__ TP = reinterpret_cast<T4*>(smem);  // [elay] top-face contributions (per thread)
-      T* __restrict__ P = reinterpret_cast<T*>(TP + elay);  // [3 slots][2][lay] f0, f1
-      T* __restrict__ S = P + 6 * lay;                      // [4][slay] sums for plane k
-      T* __restrict__ Q = S + 4 * slay;                     // [2 slots][2][nc] f2, f3 on plane k
-      // [2 slots][elay] conductivities, 8-byte aligned after Q
-      TS* __restrict__ SG = reinterpret_cast<TS*>(
-          smem + (((size_t)elay * sizeof(T4) + (size_t)(6 * lay + 4 * slay + 4 * nc) * sizeof(T) + 7) & ~(size_t)7));
-      // loads of plane kp of f0, f1 into ring slot sl, of layer kl's
-      // conductivities and of f2, f3 on plane kq into slot parity
+      T* __restrict__ P = reinterpret_cast<T*>(smem);  // [3 slots][2][layp] f0, f1
+      T* __restrict__ S = P + 6 * layp;                // [4][slay] sums for plane k
       auto load_plane = [&](int kp, int sl) {
         const size_t base = (size_t)kp * plane + gn0;
-        dma_dwords(reinterpret_cast<const STM_GLOBAL unsigned*>(g0 + base), P + (2 * sl) * lay, WT * lay);
-        dma_dwords(reinterpret_cast<const STM_GLOBAL unsigned*>(g1 + base), P + (2 * sl + 1) * lay, WT * lay);
+        if (COH && G > 1)
+          dma_words<kDeviceScope>(reinterpret_cast<const STM_GLOBAL unsigned*>(g0 + base), P + (2 * sl) * layp,
+                                  WT * lay, wfirst);
+        else
+          dma_words(reinterpret_cast<const STM_GLOBAL unsigned*>(g0 + base), P + (2 * sl) * layp, WT * lay, wfirst);
+        dma_words(reinterpret_cast<const STM_GLOBAL unsigned*>(g1 + base), P + (2 * sl + 1) * layp, WT * lay, wfirst);
       };
-      auto load_sigma = [&](int kl) {
-        dma_dwords(reinterpret_cast<const STM_GLOBAL unsigned*>(sg + (size_t)kl * eplane + ge0), SG + (kl & 1) * elay,
-                   WS * elay);
-      };
-      auto load_q = [&](int kq) {
-        T* qs = Q + (kq & 1) * 2 * nc;
-        if (f2) dma_dwords(reinterpret_cast<const STM_GLOBAL unsigned*>(g2 + (size_t)kq * plane + go0), qs, WT * nc);
-        if (f3) dma_dwords(reinterpret_cast<const STM_GLOBAL unsigned*>(g3 + (size_t)kq * plane + go0), qs + nc, WT * nc);
-      };
-      // prologue: zero top-face contributions and sums (the border stays
-      // zero), planes ks and ks + 1, conductivities of layer ks, and f2, f3
-      // on plane kb0 when the march starts there
-      for (int q = tid; q < elay; q += BLOCK) TP[q] = T4{T(0), T(0), T(0), T(0)};
-      for (int q = tid; q < 4 * slay; q += BLOCK) S[q] = T(0);
-      if (!f2 || !f3)
-        for (int q = tid; q < 4 * nc; q += BLOCK) Q[q] = T(0);
-      __syncthreads();
+      // prologue: planes ks and ks + 1, conductivities of layer ks, a zero
+      // border around the sums, the thread's columns
       load_plane(ks, 0);
       load_plane(ks + 1, 1);
-      load_sigma(ks);
-      if (ks == kb0) load_q(kb0);
+      int eo[kCE];                 // staged node of the element's vertex (0, 0)
+      int es[kCE];                 // its sum slot
+      unsigned qe[kCE], qn[kCB];   // the columns' numbers in the tile's layer and plane
+      TS sc[kCE];
+      T kb[kCE][4], mb[kCE][4];    // x-y transforms of the layer's bottom face
+      T ac[kCE][4];                // top half of the layer below
+#pragma unroll
+      for (int n = 0; n < kCE; ++n) {
+        // columns past the tile read column 0's values and write nothing
+        const int q = tid + n * BLOCK, qq = q < elay ? q : 0;
+        const int r = (int)fdiv(qq, mex);
+        qe[n] = qq;
+        eo[n] = qq + r;
+        es[n] = eo[n] + r + EXP + 1;
+        sc[n] = sg[(size_t)ks * eplane + ge0 + qq];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ac[n][v] = T(0);
+      }
+      int no[kCB], ns[kCB];        // staged node and lower left sum slot of the output nodes
+#pragma unroll
+      for (int n = 0; n < kCB; ++n) {
+        const int q = tid + n * BLOCK, qq = q < nc ? q : 0;
+        const int r = (int)fdiv(qq, mnx);
+        qn[n] = qq;
+        no[n] = (j0 - jr0) * nx + qq;
+        ns[n] = (j0 - jr0 + r) * EXP + (qq - r * nx);
+      }
+      for (int q = tid; q < 4 * (2 * EXP + 2 * erows); q += BLOCK) {
+        const int v = q & 3, b = q >> 2;
+        const int at = b < EXP ? b
+                       : b < 2 * EXP ? (erows + 1) * EXP + (b - EXP)
+                                     : (1 + ((b - 2 * EXP) >> 1)) * EXP + (((b - 2 * EXP) & 1) ? EXP - 1 : 0);
+        S[v * slay + at] = T(0);
+      }
+      auto corners = [&](const T* __restrict__ a, int o, T (&x)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = a[o + (v & 1) + (v >> 1) * nx];
+      };
+      auto face = [&](const T (&x0)[4], const T (&x1)[4], T (&kf)[4], T (&mf)[4]) {
+        T kv[4], mv[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if constexpr (IsKScale<KV>::value)
+            kv[v] = x0[v];
+          else
+            kv[v] = kval(x0[v], x1[v]);
+          mv[v] = mval(x0[v], x1[v]);
+        }
+        face_transform<T>(kv, kf);
+        face_transform<T>(mv, mf);
+      };
+      __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
+#pragma unroll
+      for (int n = 0; n < kCE; ++n) {
+        if (wfirst + n * BLOCK >= elay) continue;
+        T x0[4], x1[4];
+        corners(P, eo[n], x0);
+        corners(P + layp, eo[n], x1);
+        face(x0, x1, kb[n], mb[n]);
+      }
+      // the layer's fibre row (uniform: scalar loads, a step ahead of their use)
+      // folded with the element constants; each factor is affine in the conductivity
+      double fc2 = fib[kFibStride * ks], fs2 = fib[kFibStride * ks + 1], fcs = fib[kFibStride * ks + 2];
       int s0 = 0;  // ring slot of plane k
       for (int k = ks; k < kb1; ++k) {
         const int s1 = s0 == 2 ? 0 : s0 + 1;
         const int s2 = s1 == 2 ? 0 : s1 + 1;
         STM_T0(t_za);
-        // ---- loads for the next step: plane k+2 and layer k+1 when layer
-        // k+1 is computed (it adds to plane k+1 < kb1); f2, f3 of the next
-        // owned plane ----
+        // ---- loads: conductivities of layer k+1 when that layer is computed
+        // (it adds to plane k+1 < kb1), f2, f3 of plane k, plane k+2 ----
+        // (a uniform address plus the column's number, which takes no vector
+        // arithmetic; a wave without an n-th column leaves its values undefined)
+        TS sn[kCE];
+        const int kn = k + 1 < min(kb1, EZ) ? k + 1 : min(k, EZ - 1);
+        const STM_GLOBAL TS* __restrict__ sgk = sg + ((size_t)kn * eplane + ge0);
+#pragma unroll
+        for (int n = 0; n < kCE; ++n)
+          if (wfirst + n * BLOCK < elay) sn[n] = sgk[qe[n]];
+        T v2[kCB], v3[kCB];
+        const size_t pk = (size_t)k * plane + go0;
+        if (k >= kb0) {
+#pragma unroll
+          for (int n = 0; n < kCB; ++n) {
+            if (wfirst + n * BLOCK < nc) {
+              if constexpr (NF > 0) v2[n] = g2[pk + qn[n]];
+              if constexpr (NF > 1) v3[n] = g3[pk + qn[n]];
+            }
+          }
+        }
         if (k + 2 <= min(kb1, nz - 1)) load_plane(k + 2, s2);
-        if (k + 1 < min(kb1, EZ)) load_sigma(k + 1);
-        if (k + 1 < kb1) load_q(k + 1);
-        const T* __restrict__ a0 = P + (2 * s0) * lay;
-        const T* __restrict__ a1 = P + (2 * s0 + 1) * lay;
-        const TS* __restrict__ sgk = SG + (k & 1) * elay;
+        const T kx1 = T(fc2) * cxx, kx0 = T(tau * fs2) * cxx;
+        const T ky1 = T(fs2) * cyy, ky0 = T(tau * fc2) * cyy;
+        const T kxy = T(fcs) * cxy;
+        fc2 = fib[kFibStride * kn];
+        fs2 = fib[kFibStride * kn + 1];
+        fcs = fib[kFibStride * kn + 2];
         // ---- phase A: element layer k ----
+        auto sums = [&](int n, const T (&pl)[4]) {
+          if (tid + n * BLOCK < elay) {
+            const T lo = pl[0] - pl[2], hi = pl[0] + pl[2], dl = pl[1] - pl[3], dh = pl[1] + pl[3];
+            S[es[n]] = lo - dl;
+            S[slay + es[n]] = lo + dl;
+            S[2 * slay + es[n]] = hi - dh;
+            S[3 * slay + es[n]] = hi + dh;
+          }
+        };
         if (k < EZ) {
-          const T* __restrict__ b0 = P + (2 * s1) * lay;
-          const T* __restrict__ b1 = P + (2 * s1 + 1) * lay;
-          // the layer's fibre row (uniform: scalar loads) folded with the
-          // element constants: ax = cxx (s c2 + tau s2), ay = cyy (s s2 + tau c2),
-          // az = czz (s zr + tau), axy = cxy (s - tau) cs for conductivity s
-          const double c2 = fib[kFibStride * k], s2 = fib[kFibStride * k + 1], cs = fib[kFibStride * k + 2];
-          const T kx1 = T(c2) * cxx, kx0 = T(tau * s2) * cxx;
-          const T ky1 = T(s2) * cyy, ky0 = T(tau * c2) * cyy;
-          const T kz1 = T(zr) * czz, kz0 = T(tau) * czz;
-          const T kxy = T(cs) * cxy, tauT = T(tau);
-          // every LDS read of an element is issued before its arithmetic (a
-          // scheduling barrier keeps the compiler from interleaving them with
-          // waits), so one LDS round trip per element
-#pragma unroll 1
-          for (int q = tid; q < elay; q += BLOCK) {
-            const int r = (int)fdiv(q, mex);
-            const int o = q + r;                // staged node of the element's vertex (0, 0)
-            const int qp = o + r + EXP + 1;     // its padded sum slot
-            T x0[8], x1[8];
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-              const int off = o + (v & 1) + ((v >> 1) & 1) * nx;
-              x0[v] = (v & 4) ? b0[off] : a0[off];
-              x1[v] = (v & 4) ? b1[off] : a1[off];
-            }
-            const TS se = sgk[q];
-            const T4 tp = TP[q];
-            __builtin_amdgcn_sched_barrier(0);
-            T kv[8], mv[8], out[8];
+          for (int n = 0; n < kCE; ++n) {
+            if (wfirst + n * BLOCK < elay) {
+              T x0[4], x1[4], kt[4], mt[4], pl[4];
+              corners(P + (2 * s1) * layp, eo[n], x0);
+              corners(P + (2 * s1 + 1) * layp, eo[n], x1);
+              face(x0, x1, kt, mt);
+              const T sT = T(sc[n]);
+              layer_apply<T>(kb[n], kt, mb[n], mt, sT * kx1 + kx0, sT * ky1 + ky0, sT * kz1 + kz0, (sT - tauT) * kxy,
+                             c1, c3, c9, ac[n], pl);
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-              if constexpr (IsKScale<KV>::value)
-                kv[v] = x0[v];
-              else
-                kv[v] = kval(x0[v], x1[v]);
-              mv[v] = mval(x0[v], x1[v]);
+              for (int v = 0; v < 4; ++v) {
+                kb[n][v] = kt[v];
+                mb[n][v] = mt[v];
+              }
+              sums(n, pl);
             }
-            const T sT = T(se);
-            elem_apply_3d<T>(kv, mv, sT * kx1 + kx0, sT * ky1 + ky0, sT * kz1 + kz0, (sT - tauT) * kxy, cm, out);
-            S[qp] = tp.x + out[0];
-            S[slay + qp] = tp.y + out[1];
-            S[2 * slay + qp] = tp.z + out[2];
-            S[3 * slay + qp] = tp.w + out[3];
-            TP[q] = T4{out[4], out[5], out[6], out[7]};
           }
         } else {
-#pragma unroll 1
-          for (int q = tid; q < elay; q += BLOCK) {
-            const int r = (int)fdiv(q, mex);
-            const int qp = q + 2 * r + EXP + 1;
-            const T4 tp = TP[q];
-            S[qp] = tp.x;
-            S[slay + qp] = tp.y;
-            S[2 * slay + qp] = tp.z;
-            S[3 * slay + qp] = tp.w;
-          }
+#pragma unroll
+          for (int n = 0; n < kCE; ++n)
+            if (wfirst + n * BLOCK < elay) sums(n, ac[n]);
         }
         STM_T1P(t_za, 6);
         STM_T0(t_zb);
         lds_barrier();
         // ---- phase B: output nodes of plane k (an owned plane) ----
-        const T* __restrict__ qk = Q + (k & 1) * 2 * nc;
-#pragma unroll 1
-        for (int q = tid; q < (k >= kb0 ? nc : 0); q += BLOCK) {
-          const int r = fdiv(q, mnx);
-          const int i = q - r * nx;
-          const int j = j0 + r;
-          // element (i - 1 + a, j - 1 + b) gives vertex (1 - a) + 2 (1 - b)
-          const int e = (j - jr0) * EXP + i;
-          const T c0 = S[3 * slay + e], c1 = S[2 * slay + e + 1];
-          const T c2 = S[slay + e + EXP], c3 = S[e + EXP + 1];
-          const int o = (j - jr0) * nx + i;
-          const T o0 = a0[o], o1 = a1[o], o2 = qk[q], o3 = qk[nc + q];
-          __builtin_amdgcn_sched_barrier(0);
-          T y = T(0);
-          y += c0;
-          y += c1;
-          y += c2;
-          y += c3;
-          body(k * plane + go0 + q, i, j, k, y, o0, o1, o2, o3);
+        T y[kCB], o0[kCB], o1[kCB];
+#pragma unroll
+        for (int n = 0; n < kCB; ++n) {
+          if (k >= kb0 && wfirst + n * BLOCK < nc) {
+            // element (i - 1 + a, j - 1 + b) gives vertex (1 - a) + 2 (1 - b)
+            const int e = ns[n];
+            y[n] = (S[3 * slay + e] + S[2 * slay + e + 1]) + (S[slay + e + EXP] + S[e + EXP + 1]);
+            o0[n] = P[(2 * s0) * layp + no[n]];
+            o1[n] = P[(2 * s0 + 1) * layp + no[n]];
+          }
         }
-        __syncthreads();  // also waits for the step's direct-to-LDS loads
+        // the step's loads, all before the first store: stores then stay in
+        // flight over the next step
+        __builtin_amdgcn_s_waitcnt(kWaitVm);
+#pragma unroll
+        for (int n = 0; n < kCE; ++n)
+          if (wfirst + n * BLOCK < elay) sc[n] = sn[n];
+#pragma unroll
+        for (int n = 0; n < kCB; ++n) {
+          const int q = tid + n * BLOCK;
+          if (k >= kb0 && q < nc) {
+            const int r = (int)fdiv(q, mnx);
+            body(NodeAt{(int)pk, (unsigned)q}, q - r * nx, j0 + r, k, y[n], o0[n], o1[n], v2[n], v3[n]);
+          }
+        }
+        lds_barrier();
         STM_T1P(t_zb, 7);
         s0 = s1;
       }
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
     }
   }
 
-  // n dwords from global memory to LDS by direct-to-LDS loads: lane i of the
-  // wave whose first thread is w writes dword w + i + c BLOCK of the range
-  // (the LDS address of a wave's load is uniform; lanes past n do not load).
-  // Complete after the next workgroup barrier that follows a fence.
-  __device__ __forceinline__ void dma_dwords(const STM_GLOBAL unsigned* __restrict__ src, void* dst, int n) const {
-    const int tid = threadIdx.x;
+  // n dwords from global memory to LDS by direct-to-LDS loads of 16 bytes a
+  // lane (the last n % 4 dwords one a lane): lane i of the wave whose first
+  // thread is w writes 16-byte word w + i + c BLOCK of the range (the LDS
+  // address of a wave's load is uniform; lanes past the end do not load).  dst
+  // is 16-byte aligned, src 4-byte.  Complete for every wave after a barrier
+  // before which each has waited for its vector memory operations.
+  template <int AUX = 0>
+  __device__ __forceinline__ void dma_words(const STM_GLOBAL unsigned* __restrict__ src, void* dst, int n,
+                                            int wfirst) const {
+    const unsigned lane4 = 4 * threadIdx.x;
     unsigned* d = reinterpret_cast<unsigned*>(dst);
-    const int wbase = tid & ~(kWave - 1);
-    for (int c0 = 0; c0 < n; c0 += BLOCK) {
-      if (c0 + tid < n)
-        __builtin_amdgcn_global_load_lds(src + c0 + tid, (__attribute__((address_space(3))) void*)(d + c0 + wbase), 4,
-                                         0, 0);
+    const int n4 = n >> 2;
+    for (int c0 = 0; c0 + wfirst < n4; c0 += BLOCK) {
+      if (c0 + (int)threadIdx.x < n4)
+        __builtin_amdgcn_global_load_lds(src + 4 * c0 + lane4,
+                                         (__attribute__((address_space(3))) void*)(d + 4 * (c0 + wfirst)), 16, 0, AUX);
     }
+    if (wfirst == 0 && (int)threadIdx.x < (n & 3))
+      __builtin_amdgcn_global_load_lds(src + 4 * n4 + (unsigned)threadIdx.x,
+                                       (__attribute__((address_space(3))) void*)(d + 4 * n4), 4, 0, AUX);
   }
-  // Workgroup barrier ordering LDS accesses only: direct-to-LDS loads in
+  // Workgroup barrier ordering LDS accesses only: vector memory operations in
   // flight stay in flight (a fence would wait for them).
   __device__ __forceinline__ void lds_barrier() const { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -794,8 +941,7 @@ struct Team {
           }
 #pragma unroll
           for (int h = 0; h < UA; ++h) {
-            if constexpr (DIM == 3) elem_apply_3d<T>(kv[h], mv[h], D[h], cxx, cyy, czz, cxy, cm, out[h]);
-            else elem_apply_2d<T>(kv[h], mv[h], D[h], cxx, cyy, cm, out[h]);
+            elem_apply_2d<T>(kv[h], mv[h], D[h], cxx, cyy, cm, out[h]);
           }
 #pragma unroll
           for (int h = 0; h < UA; ++h) {
@@ -844,7 +990,7 @@ struct Team {
             }
           }
           const int o = (((DIM == 3) ? (k - kr0) : 0) * sy + (j - jr0)) * nx + i;
-          body(idx, i, j, k, y, l0[o], l1[o], f2 ? l2[o] : T(0), f3 ? l3[o] : T(0));
+          body(NodeAt{0, (unsigned)idx}, i, j, k, y, l0[o], l1[o], f2 ? l2[o] : T(0), f3 ? l3[o] : T(0));
         }
         __syncthreads();
       }
@@ -991,7 +1137,7 @@ struct Team {
       sync();
       return;
     }
-    staged<TI>(
+    staged<TI, 2>(
         l, x, w, b, di, KScale<TI>{TI(prm.theta)}, [](TI a, TI ww) { return ww * a; },
         [&](int idx, int, int, int, TI y, TI xo, TI, TI bo, TI dio) { gmem(out)[idx] = xo + om * (bo - y) * dio; });
   }
@@ -1004,11 +1150,12 @@ struct Team {
   // the same operations in the same order as in the pass that owns them, so the
   // result equals two single sweeps.  x == null stands for the sweep from zero,
   // x = om0 b dinv, formed while staging (three sweeps in the pass).  out must
-  // not alias x.  last: fin(node, value) takes every result, and the closing
-  // team barrier is left to the caller's reduction.
+  // not alias x.  coh: x and out are exchanged past the caches (halo_barrier
+  // closes the pass).  last: fin(node, value) takes every result, and the
+  // closing team barrier is left to the caller's reduction.
   template <typename Fin>
   __device__ __forceinline__ void jacobi_pair(const TI* __restrict__ x, const TI* __restrict__ b, TI* __restrict__ out, TI om0,
-                              TI om1, TI om2, bool last, Fin fin) const {
+                              TI om1, TI om2, bool coh, bool last, Fin fin) const {
     static_assert(DIM == 2, "the fused sweep pair is 2D");
     using T = TI;
     constexpr int NV = 4;
@@ -1051,7 +1198,7 @@ struct Team {
         for (int u = 0; u < U; ++u) {
           const int q = qb + u * BLOCK;
           if (q < nst) {
-            if (x) r0[u] = x[gq0 + q];
+            if (x) r0[u] = coh ? __hip_atomic_load(x + gq0 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : x[gq0 + q];
             r1[u] = w[gq0 + q];
             r2[u] = b[gq0 + q];
             r3[u] = di[gq0 + q];
@@ -1155,14 +1302,22 @@ struct Team {
           if (sweep == 0) {
             lx1[o] = xn;
           } else {
-            out[j * nx + i] = xn;
-            if (last) fin(j * nx + i, xn);
+            if (coh)
+              __hip_atomic_store(out + j * nx + i, xn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+              out[j * nx + i] = xn;
+            if (last) fin(NodeAt{0, (unsigned)(j * nx + i)}, xn);
           }
         }
         __syncthreads();
       }
     }
-    if (G > 1 && !last) team_barrier();
+    if (!last) {
+      if (coh)
+        halo_barrier();
+      else if (G > 1)
+        team_barrier();
+    }
   }
 
   // Every sweep of the smoother in one pass, for a one-workgroup team whose
@@ -1244,7 +1399,7 @@ struct Team {
       for (int q = threadIdx.x; q < nst; q += BLOCK) {
         const T xn = om * lb[q] * ld[q];
         dst[q] = xn;
-        if (nc == 1) fin(q, xn);
+        if (nc == 1) fin(NodeAt{0, (unsigned)q}, xn);
       }
       __syncthreads();
     }
@@ -1307,7 +1462,7 @@ struct Team {
         const T xn = cur[q] + om * (lb[q] - y) * ld[q];
         if (s == nc) {
           out[q] = xn;
-          fin(q, xn);
+          fin(NodeAt{0, (unsigned)q}, xn);
         } else {
           nxt[q] = xn;
         }
@@ -1320,7 +1475,7 @@ struct Team {
     const int n = L->g[l].n;
     bytes = uni(bytes + (4.0 * sizeof(TI) * n + dbytes(l)));
     const TI* __restrict__ w = mgW(l);
-    staged<TI>(
+    staged<TI, 1>(
         l, x, w, b, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
         [](TI a, TI ww) { return ww * a; }, [&](int idx, int, int, int, TI y, TI, TI, TI bo, TI) { gmem(out)[idx] = bo - y; });
   }
@@ -1406,7 +1561,7 @@ struct Team {
         // pass each), and a single sweep when one is left.  Pass t (1-based) of
         // P writes buf[(P - t + 1) % 2]: the last one out0.
         if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
-          jacobi_resident(b0, out0, nc, 0, [](int, TI) {});
+          jacobi_resident(b0, out0, nc, 0, [](NodeAt, TI) {});
           return;
         }
         // With three or more sweeps the first pass runs sweeps 1 to 3 (the sweep
@@ -1415,7 +1570,8 @@ struct Team {
         const int P = nc - np - (nc >= 3 ? 1 : 0);
         int s, t;
         if (nc >= 3) {
-          jacobi_pair(nullptr, b0, buf[P % 2], wgt(0, 0), wgt(0, 1), wgt(0, 2), false, [](int, TI) {});
+          jacobi_pair(nullptr, b0, buf[P % 2], wgt(0, 0), wgt(0, 1), wgt(0, 2), false, false,
+                      [](NodeAt, TI) {});
           s = 4;
         } else {
           jacobi(0, b0, nullptr, buf[P % 2], wgt(0, 0));
@@ -1424,7 +1580,7 @@ struct Team {
         t = 2;
         for (; s + 1 <= nc; s += 2, ++t)
           jacobi_pair(buf[(P - t + 2) % 2], b0, buf[(P - t + 1) % 2], TI(0), wgt(0, s - 1), wgt(0, s), false,
-                      [](int, TI) {});
+                      false, [](NodeAt, TI) {});
         for (; s <= nc; ++s, ++t) jacobi(0, b0, buf[(P - t + 2) % 2], buf[(P - t + 1) % 2], wgt(0, s - 1));
       }
       return;
@@ -1477,14 +1633,15 @@ struct Team {
         const TI om = wgt(1, s - 1);
         const bool last = s == nc;
         bytes = uni(bytes + (5.0 * sizeof(TI) * n + dbytes(0)));
-        staged<TI>(
+        staged<TI, 2, true>(
             0, x, w, b0, dinv, KScale<TI>{TI(prm.theta)}, [](TI a, TI ww) { return ww * a; },
-            [&](int idx, int, int, int, TI y, TI xo, TI, TI bo, TI dio) {
+            [&](NodeAt at, int, int, int, TI y, TI xo, TI, TI bo, TI dio) {
               const TI xn = xo + om * (bo - y) * dio;
-              gmem(out)[idx] = xn;
-              if (last) fin(idx, xn);
+              coh_store(&node_ref(out, at), xn);
+              if (last) fin(at, xn);
             },
-            !last);
+            false);
+        if (!last) halo_barrier();
       }
     } else {
       if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
@@ -1495,7 +1652,7 @@ struct Team {
 #pragma unroll 1
       for (int t = 1; t <= P; ++t)
         jacobi_pair(t == 1 ? nullptr : buf[(P - t) % 2], b0, buf[(P - t + 1) % 2], wgt(1, 0), wgt(1, 2 * t - 1),
-                    wgt(1, 2 * t), t == P, fin);
+                    wgt(1, 2 * t), G > 1, t == P, fin);
     }
   }
 
@@ -1581,7 +1738,7 @@ struct Team {
     // the iterate is scaled to norm 1 by the pass that reads it next
     for (int it = 0; it < prm.power_iters; ++it) {
       double nn[2] = {0.0, 0.0};
-      staged<TI>(
+      staged<TI, 1>(
           l, x0, w, di, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
           [](TI a, TI ww) { return ww * a; },
           [&](int idx, int, int, int, TI ax, TI xown, TI, TI dio, TI) {
@@ -1601,7 +1758,449 @@ struct Team {
     bytes = uni(bytes + (prm.power_iters * (5.0 * sizeof(TI) * g.n + dbytes(l))));
     return lam;
   }
+  // Residual of the slab (float64) -> V_0 = -R, reaction weights and inverse
+  // diagonal on every grid; its squared 2-norm into io.resid.
+  __device__ __forceinline__ void residual_step(StepIO& io) const {
+    const GridDev& g0 = L->g[0];
+    const int n0 = g0.n;
+    const double th = prm.theta, inv_dt = uni(1.0 / L->dt), kr = prm.k_react, ar = prm.a_react;
+    TI* V0 = V;
+    TI* w0 = mgW(0);
+    TI* __restrict__ di = dinv;
+    TI* x1 = io.x1 ? mgT(0) : nullptr;
+    const TI om1 = x1 ? wgt(1, 0) : TI(0);
+    double rr[1] = {0.0};
+    bytes = uni(bytes + (24.0 * n0 + 8.0 * g0.ne + (x1 ? 4.0 : 3.0) * sizeof(TI) * n0));
+    for (int l = 1; l < (MG ? L->nmg : 1); ++l) bytes = uni(bytes + ((8.0 + sizeof(TI)) * L->g[l].n));
+    const double cmd = (DIM == 3) ? 8.0 * g0.hx * g0.hy * g0.hz / 216.0 : 4.0 * g0.hx * g0.hy / 36.0;
+    staged<double, 1>(
+        0, (const double*)io.u, (const double*)io.uprev, (const double*)kdiag0, (const double*)nullptr,
+        [th](double a, double b) { return th * a + (1.0 - th) * b; },
+        [&](double a, double b) { return (a - b) * inv_dt - react(a, kr, ar); },
+        [&](NodeAt at, int i, int j, int k, double y, double uown, double, double kd, double) {
+          const double r = -y;
+          const double w = inv_dt - react_d(uown, kr, ar);
+          const TI dd = TI(1.0 / (th * kd + nel(0, i, j, k) * cmd * w));
+          node_ref(V0, at) = TI(r);
+          node_ref(w0, at) = TI(w);
+          node_ref(di, at) = dd;
+          if constexpr (DIM == 3 && !MG) {
+            if (x1) node_ref(x1, at) = om1 * TI(r) * dd;
+          }
+          rr[0] += r * r;
+        },
+        false);
+    coarse_weights(io.u, inv_dt);
+    tsum<1>(rr);  // its barriers also publish the writes above
+    io.resid = rr[0];
+  }
+
+  // Defect correction u += P(A) r, P the Chebyshev sweeps; max-norm into io.dmax.
+  __device__ __forceinline__ void correct_step(StepIO& io) const {
+    double dm = 0.0;
+    double* __restrict__ u = io.u;
+    bytes = uni(bytes + 16.0 * L->g[0].n);
+    chebyshev(V, Z, io.nc, io.x1 != 0, [&](NodeAt at, TI xn) {
+      const double dl = double(xn);
+      node_ref(u, at) += dl;
+      dm = fmax(dm, fabs(dl));
+    });
+    io.dmax = tmax(dm);  // its barrier also publishes u to the other members
+  }
+
+  // Newton step by GMRES(restart), right-preconditioned by the V-cycle (or the
+  // sweeps), from the residual in V_0: u += delta, its max-norm and the relative
+  // residual reached into io.
+  __device__ __forceinline__ void gmres_step(StepIO& io) const {
+    __shared__ double H[(kMaxRestart + 1) * kMaxRestart];
+    __shared__ double cs_[kMaxRestart], sn_[kMaxRestart], gv[kMaxRestart + 1], sc[kMaxRestart + 1];
+    __shared__ double yv[kMaxRestart], coef[kMaxRestart + 1];
+    __shared__ double sh_resid;
+#ifdef STM_PHASE_TIMERS
+    long long* ph_acc = ph;
+#endif
+    double* __restrict__ u = io.u;
+    double* __restrict__ dlt = io.dlt;
+    const double beta = io.beta, eta = io.eta, krylov_words = io.krylov_words;
+    double model_bytes = io.model_bytes;
+    const int tid = threadIdx.x, n0 = L->g[0].n, nb = nband(), restart = prm.restart;
+    const int64_t vs = vstride;
+            // ---- GMRES(restart), right-preconditioned by the V-cycle ----
+            if (tid == 0) {
+              sc[0] = 1.0 / beta;
+              gv[0] = beta;
+            }
+            __syncthreads();
+            const double tol_abs = uni(eta * beta);
+            int jdim = 0;
+            for (int j = 0; j < restart; ++j) {
+              TI* Vj = V + j * vs;
+              TI* Zj = Z + j * vs;
+              TI* Vn = V + (j + 1) * vs;
+              model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * (krylov_words + 2.0 * j));
+              STM_T0(t_vc);
+              vcycle(Vj, Zj);
+              STM_T1(t_vc, 1);
+              STM_T0(t_pa);
+              // pass A: ws = A Z_j (into V_{j+1})
+              bytes = uni(bytes + (3.0 * sizeof(TI) * n0 + dbytes(0)));
+              staged<TI, 0>(
+                  0, Zj, mgW(0), (const TI*)nullptr, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
+                  [](TI a, TI ww) { return ww * a; },
+                  [&](int idx, int, int, int, TI w, TI, TI, TI, TI) { gmem(Vn)[idx] = w; });
+              STM_T1(t_pa, 2);
+              // Classical Gram-Schmidt against V_0..V_j, done twice when the inner
+              // vectors are float32 (CGS2: the second pass restores the orthogonality
+              // the first loses to rounding); each pass adds its projections to
+              // column j of H.
+              double nn[1] = {0.0};
+              constexpr int kPasses = sizeof(TI) == 4 ? 2 : 1;
+              // dots of the next pass, accumulated by the first pass's update
+              double dnext[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+              bool have_dots = false;
+    #pragma unroll 1
+              for (int pass = 0; pass < kPasses; ++pass) {
+                STM_T0(t_dot);
+                // dots with V_0..V_min(j,7) over the owned nodes: batched loads
+                double d[9];
+    #pragma unroll
+                for (int q = 0; q < 9; ++q) d[q] = have_dots ? dnext[q] : 0.0;
+                const int nk0 = min(j + 1, 8);
+                if (!have_dots) {
+                  bytes = uni(bytes + ((1.0 + nk0) * sizeof(TI) * n0));
+                  const TI* __restrict__ Vb = V;
+                  const TI* __restrict__ Vr = Vn;
+                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+                    TI wv[2], vv[2][8];
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu) {
+                      const int q = qb + uu * BLOCK;
+                      const int idx = q < nb ? bidx(q) : 0;
+                      wv[uu] = q < nb ? Vr[idx] : TI(0);
+    #pragma unroll
+                      for (int p = 0; p < 8; ++p) vv[uu][p] = (p < nk0 && q < nb) ? Vb[p * vs + idx] : TI(0);
+                    }
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu)
+    #pragma unroll
+                      for (int p = 0; p < 8; ++p) d[p] += double(vv[uu][p]) * double(wv[uu]);
+                  }
+                }
+                tsum<9>(d);
+                if (tid == 0) {
+    #pragma unroll
+                  for (int q = 0; q < 8; ++q)
+                    if (q < nk0) coef[q] = d[q];
+                }
+                for (int k0 = 8; k0 <= j; k0 += 8) {  // remaining dot chunks
+                  const int nk = min(j + 1 - k0, 8);
+                  bytes = uni(bytes + ((1.0 + nk) * sizeof(TI) * n0));
+    #pragma unroll
+                  for (int q = 0; q < 9; ++q) d[q] = 0.0;
+                  for (int q = tid; q < nb; q += BLOCK) {
+                    const int idx = bidx(q);
+                    const double wd = double(Vn[idx]);
+    #pragma unroll
+                    for (int p = 0; p < 8; ++p)
+                      if (p < nk) d[p] += double(V[(k0 + p) * vs + idx]) * wd;
+                  }
+                  tsum<9>(d);
+                  if (tid == 0) {
+    #pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                      if (q < nk) coef[k0 + q] = d[q];
+                  }
+                }
+                // projections onto the normalised basis enter H; V_q is stored with
+                // norm 1/sc[q], so w loses (sc[q]^2 <V_q, w>) V_q
+                if (tid == 0)
+                  for (int q = 0; q <= j; ++q) {
+                    const double hq = sc[q] * sc[j] * coef[q];
+                    H[q * kMaxRestart + j] = (pass ? H[q * kMaxRestart + j] : 0.0) + hq;
+                    coef[q] = sc[q] * sc[q] * coef[q];
+                  }
+                __syncthreads();
+                STM_T1(t_dot, 3);
+                STM_T0(t_pb);
+                // pass B: V_{j+1} -= sum_q coef_q V_q over the owned nodes; norm
+                nn[0] = 0.0;
+                bytes = uni(bytes + ((j + 3.0) * sizeof(TI) * n0));
+                // The first of two passes with at most 8 basis vectors also forms
+                // the second pass's dots from the values it holds: the same nodes
+                // per thread, the same operations in the same order as the
+                // separate loops, one read of the vectors fewer.
+                const bool fuse = pass + 1 < kPasses && j < 8;
+                if (fuse) {
+    #pragma unroll
+                  for (int q = 0; q < 9; ++q) dnext[q] = 0.0;
+                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+                    double w[2];
+                    int ix[2];
+                    TI vv[2][8];
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu) {
+                      const int q = qb + uu * BLOCK;
+                      ix[uu] = q < nb ? bidx(q) : 0;
+                      w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
+    #pragma unroll
+                      for (int p = 0; p < 8; ++p) vv[uu][p] = (p <= j && q < nb) ? V[p * vs + ix[uu]] : TI(0);
+                    }
+    #pragma unroll
+                    for (int p = 0; p < 8; ++p) {
+                      const double cq = p <= j ? coef[p] : 0.0;
+    #pragma unroll
+                      for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[uu][p]);
+                    }
+                    TI wt[2];
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu) {
+                      wt[uu] = TI(0);
+                      if (qb + uu * BLOCK < nb) {
+                        wt[uu] = TI(w[uu]);
+                        Vn[ix[uu]] = wt[uu];
+                      }
+                    }
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu)
+    #pragma unroll
+                      for (int p = 0; p < 8; ++p) dnext[p] += double(vv[uu][p]) * double(wt[uu]);
+                  }
+                } else {
+                  // vectors in chunks of 4, all loads of a chunk issued before use
+                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+                    double w[2];
+                    int ix[2];
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu) {
+                      const int q = qb + uu * BLOCK;
+                      ix[uu] = q < nb ? bidx(q) : 0;
+                      w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
+                    }
+                    for (int q0 = 0; q0 <= j; q0 += 4) {
+                      TI vv[4][2];
+    #pragma unroll
+                      for (int p = 0; p < 4; ++p)
+    #pragma unroll
+                        for (int uu = 0; uu < 2; ++uu)
+                          vv[p][uu] = (q0 + p <= j) ? V[(q0 + p) * vs + ix[uu]] : TI(0);
+    #pragma unroll
+                      for (int p = 0; p < 4; ++p) {
+                        const double cq = (q0 + p <= j) ? coef[q0 + p] : 0.0;
+    #pragma unroll
+                        for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[p][uu]);
+                      }
+                    }
+    #pragma unroll
+                    for (int uu = 0; uu < 2; ++uu) {
+                      if (qb + uu * BLOCK < nb) {
+                        const TI wt = TI(w[uu]);
+                        Vn[ix[uu]] = wt;
+                        nn[0] += double(wt) * double(wt);
+                      }
+                    }
+                  }
+                }
+                // Only the last pass's norm is used.  A member reads V_{j+1} at
+                // its own nodes only, and in the same thread-to-node order as it
+                // wrote them, so the first pass ends with a workgroup barrier.
+                have_dots = fuse;
+                if (pass + 1 < kPasses)
+                  __syncthreads();
+                else
+                  tsum<1>(nn);
+                STM_T1(t_pb, 4);
+              }
+              const double hn = uni(sqrt(nn[0]));
+              if (tid == 0) {
+                const double hj1 = sc[j] * hn;
+                sc[j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
+                for (int q = 0; q < j; ++q) {  // previous rotations on column j
+                  const double a = H[q * kMaxRestart + j], b = H[(q + 1) * kMaxRestart + j];
+                  H[q * kMaxRestart + j] = cs_[q] * a + sn_[q] * b;
+                  H[(q + 1) * kMaxRestart + j] = -sn_[q] * a + cs_[q] * b;
+                }
+                const double a = H[j * kMaxRestart + j];
+                const double r = sqrt(a * a + hj1 * hj1);
+                const double c = r > 0.0 ? a / r : 1.0, sn = r > 0.0 ? hj1 / r : 0.0;
+                cs_[j] = c;
+                sn_[j] = sn;
+                H[j * kMaxRestart + j] = r;
+                H[(j + 1) * kMaxRestart + j] = 0.0;
+                gv[j + 1] = -sn * gv[j];
+                gv[j] = c * gv[j];
+                sh_resid = fabs(gv[j + 1]);
+              }
+              __syncthreads();
+              jdim = j + 1;
+              const double resid = uni(sh_resid);
+              if (!(resid > tol_abs) || !(hn > 0.0)) break;
+            }
+            io.jdim = jdim;
+            if (tid == 0) {
+              for (int q = jdim - 1; q >= 0; --q) {
+                double acc = gv[q];
+                for (int p = q + 1; p < jdim; ++p) acc -= H[q * kMaxRestart + p] * yv[p];
+                yv[q] = acc / H[q * kMaxRestart + q];
+              }
+              for (int q = 0; q < jdim; ++q) coef[q] = yv[q] * sc[q];
+            }
+            __syncthreads();
+            // ---- u += sum_q y_q z_q (float64) over the owned nodes, max-norm of the step ----
+            STM_T0(t_up);
+            double dm = 0.0;
+            bytes = uni(bytes + (double(jdim) * sizeof(TI) * n0 + 24.0 * n0));
+            for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+              double dl[2] = {0.0, 0.0}, uo[2];
+              int ix[2];
+    #pragma unroll
+              for (int v = 0; v < 2; ++v) {
+                const int q = qb + v * BLOCK;
+                ix[v] = q < nb ? bidx(q) : 0;
+                uo[v] = q < nb ? u[ix[v]] : 0.0;
+              }
+              for (int q0 = 0; q0 < jdim; q0 += 4) {
+                TI zz[4][2];
+    #pragma unroll
+                for (int p = 0; p < 4; ++p)
+    #pragma unroll
+                  for (int v = 0; v < 2; ++v) zz[p][v] = (q0 + p < jdim) ? Z[(q0 + p) * vs + ix[v]] : TI(0);
+    #pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                  const double cq = (q0 + p < jdim) ? coef[q0 + p] : 0.0;
+    #pragma unroll
+                  for (int v = 0; v < 2; ++v) dl[v] += cq * double(zz[p][v]);
+                }
+              }
+    #pragma unroll
+              for (int v = 0; v < 2; ++v) {
+                if (qb + v * BLOCK < nb) {
+                  u[ix[v]] = uo[v] + dl[v];
+                  dlt[ix[v]] = dl[v];
+                  dm = fmax(dm, fabs(dl[v]));
+                }
+              }
+            }
+            io.dmax = uni(tmax(dm));  // its barrier also publishes u to the other members
+    STM_T1(t_up, 5);
+    io.model_bytes = model_bytes;
+    io.resid = sh_resid;
+  }
+
+  // lmax of grid l's D^-1 A into the weights of its sweeps; returns lmax.
+  __device__ __forceinline__ double sweep_weights(int l) const {
+    TI* x0 = (l == 0) ? V + vstride : mgX(l);
+    TI* x1 = (l == 0) ? V + 2 * vstride : mgT(l);
+    const double lmax = 1.05 * power_lmax(l, x0, x1);
+    const int K = (l == L->nmg - 1) ? L->sweeps : prm.smooth_steps;
+    if (threadIdx.x == 0) chebyshev_weights(lmax / L->cheb_ratio, lmax, K, omega + l * kMaxSweeps);
+    return lmax;
+  }
 };
+
+// The steps of a 3D solve are functions, called and not inlined, so that each
+// gets registers of its own: in one kernel with all of them inlined the state
+// of the whole solve (every pass's tile sizes and addresses) is live in every
+// pass, and the z-steps spill (780 SGPRs to VGPR lanes and 100-130 VGPRs).  The
+// team's state goes through LDS, from where the callee takes it back into
+// scalar registers; a call costs about 2 us.
+enum { kStepSetup, kStepSpectrum, kStepResidual, kStepCorrect, kStepGmres };
+#define STM_LDS __attribute__((address_space(3)))
+
+template <typename TM>
+struct CallState {
+  TM tm;
+  StepIO io;
+};
+
+template <typename T>
+__device__ __forceinline__ T lds_uniform(const STM_LDS T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
+  unsigned w[sizeof(T) / 4];
+  const STM_LDS unsigned* q = (const STM_LDS unsigned*)p;
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(q[i]);
+  T r;
+  __builtin_memcpy(&r, w, sizeof(T));
+  return r;
+}
+
+template <int WHAT, typename TM>
+__device__ __forceinline__ void run_step(const TM& tm, StepIO& io) {
+  if constexpr (WHAT == kStepSetup) {
+    tm.setup_operator();
+  } else if constexpr (WHAT == kStepSpectrum) {
+    io.dmax = tm.sweep_weights(0);
+    io.resid = tm.spectrum_low();
+  } else if constexpr (WHAT == kStepResidual) {
+    tm.residual_step(io);
+  } else if constexpr (WHAT == kStepCorrect) {
+    tm.correct_step(io);
+  } else {
+    tm.gmres_step(io);
+  }
+}
+
+template <int WHAT, typename TI, int DIM, int BLOCK>
+__device__ __attribute__((noinline)) void step_function(STM_LDS CallState<Team<TI, DIM, BLOCK, false>>* st,
+                                                        STM_LDS unsigned char* smem, STM_LDS double* red,
+                                                        STM_LDS double* omega) {
+  auto scalar = [](auto* p) { return (decltype(p))(size_t)__builtin_amdgcn_readfirstlane((int)(size_t)p); };
+  st = scalar(st);
+  Team<TI, DIM, BLOCK, false> tm = lds_uniform(&st->tm);
+  StepIO io = lds_uniform(&st->io);
+  tm.smem = (unsigned char*)scalar(smem);
+  tm.red = (double*)scalar(red);
+  tm.omega = (double*)scalar(omega);
+  __syncthreads();  // every wave has read the state
+  run_step<WHAT>(tm, io);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    st->tm.gen = tm.gen;
+    st->tm.hgen = tm.hgen;
+    st->tm.rslot = tm.rslot;
+    st->tm.broken = tm.broken;
+    st->tm.bytes = tm.bytes;
+    st->io.model_bytes = io.model_bytes;
+    st->io.dmax = io.dmax;
+    st->io.resid = io.resid;
+    st->io.jdim = io.jdim;
+  }
+  __syncthreads();
+}
+
+// A step of the solve: called on single-grid 3D teams, inlined elsewhere.  st->tm
+// holds the sample's team state (its counters are those of the last call).
+template <int WHAT, typename TI, int DIM, int BLOCK, bool MG>
+__device__ __forceinline__ void do_step(const Team<TI, DIM, BLOCK, MG>& tm, StepIO& io,
+                                     CallState<Team<TI, DIM, BLOCK, MG>>* st, unsigned char* smem, double* red,
+                                     double* omega) {
+  if constexpr (DIM == 3 && !MG) {
+    auto* s3 = (STM_LDS CallState<Team<TI, DIM, BLOCK, MG>>*)st;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      s3->tm.gen = tm.gen;
+      s3->tm.hgen = tm.hgen;
+      s3->tm.rslot = tm.rslot;
+      s3->tm.broken = tm.broken;
+      s3->tm.bytes = tm.bytes;
+      st->io = io;
+    }
+    __syncthreads();
+    step_function<WHAT, TI, DIM, BLOCK>(s3, (STM_LDS unsigned char*)smem, (STM_LDS double*)red,
+                                        (STM_LDS double*)omega);
+    tm.gen = __builtin_amdgcn_readfirstlane(s3->tm.gen);
+    tm.hgen = __builtin_amdgcn_readfirstlane(s3->tm.hgen);
+    tm.rslot = __builtin_amdgcn_readfirstlane(s3->tm.rslot);
+    tm.broken = __builtin_amdgcn_readfirstlane((int)s3->tm.broken) != 0;
+    tm.bytes = uni(s3->tm.bytes);
+    io.model_bytes = uni(s3->io.model_bytes);
+    io.dmax = uni(s3->io.dmax);
+    io.resid = uni(s3->io.resid);
+    io.jdim = __builtin_amdgcn_readfirstlane(s3->io.jdim);
+  } else {
+    run_step<WHAT>(tm, io);
+  }
+}
 
 template <typename TI, int DIM, int BLOCK, bool MG>
 __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restrict__ levels,
@@ -1609,11 +2208,8 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
   constexpr int NW = BLOCK / kWave;
   extern __shared__ __align__(16) unsigned char smem_dyn[];
   __shared__ double red[NW * 9];
-  __shared__ double H[(kMaxRestart + 1) * kMaxRestart];
-  __shared__ double cs_[kMaxRestart], sn_[kMaxRestart], gv[kMaxRestart + 1], sc[kMaxRestart + 1];
-  __shared__ double yv[kMaxRestart], coef[kMaxRestart + 1];
   __shared__ double omega_tab[kMaxMG * kMaxSweeps];
-  __shared__ double sh_resid;
+  __shared__ CallState<Team<TI, DIM, BLOCK, MG>> calls;
 #ifdef STM_PHASE_TIMERS
   __shared__ long long ph_acc[8];
   if (threadIdx.x < 8) ph_acc[threadIdx.x] = 0;
@@ -1638,6 +2234,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
   tm.part = task.part;
   tm.fault = task.fault;
   tm.gen = 0;
+  tm.hgen = 0;
   tm.rslot = 0;
   tm.broken = false;
 #ifdef STM_PHASE_TIMERS
@@ -1666,7 +2263,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
   const double kr = uni(prm.k_react), ar = uni(prm.a_react), tau = uni(prm.tau), thr = uni(prm.threshold);
   const double zr = uni(prm.zr);
   const double th = uni(prm.theta);
-  const int restart = prm.restart;
 
   bool have_prev = false;
   const double* prevU = nullptr;
@@ -1688,7 +2284,13 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
     if (task.u_guess) W = task.u_guess + (int64_t)s * m * n0;
     else if (have_prev) W = prevU;
 
-    tm.setup_operator();
+    if (tid == 0) calls.tm = tm;
+    StepIO io{};
+    io.u = u;
+    io.uprev = uprev;
+    io.dlt = dlt;
+    io.krylov_words = 7.0 + L->pc_words;
+    do_step<kStepSetup>(tm, io, &calls, smem_dyn, red, omega_tab);
     // initial state, activation markers, warm-start history
     tm.bytes = uni(tm.bytes + ((24.0 + sizeof(TI) + 24.0) * n0));
     for (int q = tid; q < nb; q += BLOCK) {
@@ -1707,7 +2309,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
     // (5 per sweep and per coarse-grid residual, weighted by the grid's nodes)
     // + 2j + 3 (Arnoldi step) inner words, per node
     double model_bytes = 0.0;
-    const double krylov_words = 7.0 + L->pc_words;
     double worst_final = 0.0;
     bool weights_ready = (prm.smoother == 0);
     // defect correction by Chebyshev sweeps (the default way to a Newton step
@@ -1751,41 +2352,13 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       }
       for (; it - ncor < prm.newton_max; ++it) {
         // ---- residual (float64) -> V_0, Jacobian weights on every grid ----
-        TI* V0 = tm.V;
-        TI* w0 = tm.mgW(0);
-        double rr[1] = {0.0};
+        // 3D defect corrections start with the sweep from zero, om r / diag, there
+        io.x1 = DIM == 3 && !MG && cheb;
         STM_T0(t_res);
-        // 3D defect corrections start with the sweep from zero, om r / diag, here
-        TI* x1 = (DIM == 3 && !MG && cheb) ? tm.mgT(0) : nullptr;
-        const TI om1 = x1 ? tm.wgt(1, 0) : TI(0);
-        tm.bytes = uni(tm.bytes + (24.0 * n0 + 8.0 * g0.ne + (x1 ? 4.0 : 3.0) * sizeof(TI) * n0));
-        for (int l = 1; l < L->nmg; ++l) tm.bytes = uni(tm.bytes + ((8.0 + sizeof(TI)) * L->g[l].n));
-        {
-          TI* __restrict__ di = tm.dinv;
-          const double cmd = (DIM == 3) ? 8.0 * g0.hx * g0.hy * g0.hz / 216.0 : 4.0 * g0.hx * g0.hy / 36.0;
-          tm.template staged<double>(
-              0, u, uprev, tm.kdiag0, (const double*)nullptr,
-              [th](double a, double b) { return th * a + (1.0 - th) * b; },
-              [&](double a, double b) { return (a - b) * inv_dt - react(a, kr, ar); },
-              [&](int idx, int i, int j, int k, double y, double uown, double, double kd, double) {
-                const double r = -y;
-                const double w = inv_dt - react_d(uown, kr, ar);
-                const TI dd = TI(1.0 / (th * kd + tm.nel(0, i, j, k) * cmd * w));
-                gmem(V0)[idx] = TI(r);
-                gmem(w0)[idx] = TI(w);
-                gmem(di)[idx] = dd;
-                if constexpr (DIM == 3 && !MG) {
-                  if (x1) gmem(x1)[idx] = om1 * TI(r) * dd;
-                }
-                rr[0] += r * r;
-              },
-              false);
-        }
-        tm.coarse_weights(u, inv_dt);
-        tm.template tsum<1>(rr);  // its barriers also publish the writes above
+        do_step<kStepResidual>(tm, io, &calls, smem_dyn, red, omega_tab);
         STM_T1(t_res, 0);
         model_bytes = uni(model_bytes + 32.0 * n0);
-        const double beta = uni(sqrt(rr[0]));
+        const double beta = uni(sqrt(io.resid));
         if (!isfinite(beta) && !(prm.damping && it > 0 && tstep > kMinStep)) {
           status = -5;
           break;
@@ -1803,7 +2376,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             if (beta <= beta_acc && !wide && step + trial > 0) {  // first the whole interval
               wide = true;
               nc = tm.cheb_interval(low0, lmax0, 0);
-              x1 = nullptr;
+              io.x1 = 0;
             } else {
               cheb = false;
               if (++fallbacks > kMaxFallbacks) nc = 0;
@@ -1841,16 +2414,12 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         tstep = 1.0;
         // ---- smoother weights: once per sample, from the first slab operator ----
         if (!weights_ready) {
-          for (int l = 0; l < (MG ? L->nmg : 1); ++l) {
-            TI* x0 = (l == 0) ? tm.V + vs : tm.mgX(l);
-            TI* x1 = (l == 0) ? tm.V + 2 * vs : tm.mgT(l);
-            const double lmax = 1.05 * tm.power_lmax(l, x0, x1);
-            if (l == 0) lmax0 = uni(lmax);
-            const int K = (l == L->nmg - 1) ? L->sweeps : prm.smooth_steps;
-            if (tid == 0) chebyshev_weights(lmax / L->cheb_ratio, lmax, K, omega_tab + l * kMaxSweeps);
-          }
-          if constexpr (!MG) {
-            low0 = uni(tm.spectrum_low());
+          if constexpr (MG) {
+            for (int l = 0; l < L->nmg; ++l) tm.sweep_weights(l);
+          } else {
+            do_step<kStepSpectrum>(tm, io, &calls, smem_dyn, red, omega_tab);
+            lmax0 = uni(io.dmax);
+            low0 = uni(io.resid);
             if (low0 > 0.0 && lmax0 > low0 && lmax0 < 100.0 * low0) {
               ngrow = tm.cheb_steps(low0, lmax0);
               step = min(step, ngrow);
@@ -1867,14 +2436,9 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             // ---- defect correction: u += P(A) r, P the Chebyshev sweeps ----
             model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * 5.0 * nc);
             STM_T0(t_ch);
-            double dm = 0.0;
-            tm.bytes = uni(tm.bytes + 16.0 * n0);
-            tm.chebyshev(V0, tm.Z, nc, x1 != nullptr, [&](int idx, TI xn) {
-              const double dl = double(xn);
-              gmem(u)[idx] += dl;
-              dm = fmax(dm, fabs(dl));
-            });
-            dmax = uni(tm.tmax(dm));  // its barrier also publishes u to the other members
+            io.nc = nc;
+            do_step<kStepCorrect>(tm, io, &calls, smem_dyn, red, omega_tab);
+            dmax = uni(io.dmax);
             STM_T1(t_ch, 1);
             ++krylov_total;
             ++ncor;
@@ -1915,264 +2479,15 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
           }
         }
 
-        // ---- GMRES(restart), right-preconditioned by the V-cycle ----
-        if (tid == 0) {
-          sc[0] = 1.0 / beta;
-          gv[0] = beta;
-        }
-        __syncthreads();
-        const double tol_abs = uni(eta * beta);
-        int jdim = 0;
-        for (int j = 0; j < restart; ++j) {
-          TI* Vj = tm.V + j * vs;
-          TI* Zj = tm.Z + j * vs;
-          TI* Vn = tm.V + (j + 1) * vs;
-          model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * (krylov_words + 2.0 * j));
-          STM_T0(t_vc);
-          tm.vcycle(Vj, Zj);
-          STM_T1(t_vc, 1);
-          STM_T0(t_pa);
-          // pass A: ws = A Z_j (into V_{j+1})
-          tm.bytes = uni(tm.bytes + (3.0 * sizeof(TI) * n0 + tm.dbytes(0)));
-          tm.template staged<TI>(
-              0, Zj, tm.mgW(0), (const TI*)nullptr, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
-              [](TI a, TI ww) { return ww * a; },
-              [&](int idx, int, int, int, TI w, TI, TI, TI, TI) { gmem(Vn)[idx] = w; });
-          STM_T1(t_pa, 2);
-          // Classical Gram-Schmidt against V_0..V_j, done twice when the inner
-          // vectors are float32 (CGS2: the second pass restores the orthogonality
-          // the first loses to rounding); each pass adds its projections to
-          // column j of H.
-          double nn[1] = {0.0};
-          constexpr int kPasses = sizeof(TI) == 4 ? 2 : 1;
-          // dots of the next pass, accumulated by the first pass's update
-          double dnext[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-          bool have_dots = false;
-#pragma unroll 1
-          for (int pass = 0; pass < kPasses; ++pass) {
-            STM_T0(t_dot);
-            // dots with V_0..V_min(j,7) over the owned nodes: batched loads
-            double d[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) d[q] = have_dots ? dnext[q] : 0.0;
-            const int nk0 = min(j + 1, 8);
-            if (!have_dots) {
-              tm.bytes = uni(tm.bytes + ((1.0 + nk0) * sizeof(TI) * n0));
-              const TI* __restrict__ Vb = tm.V;
-              const TI* __restrict__ Vr = Vn;
-              for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                TI wv[2], vv[2][8];
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                  const int q = qb + uu * BLOCK;
-                  const int idx = q < nb ? tm.bidx(q) : 0;
-                  wv[uu] = q < nb ? Vr[idx] : TI(0);
-#pragma unroll
-                  for (int p = 0; p < 8; ++p) vv[uu][p] = (p < nk0 && q < nb) ? Vb[p * vs + idx] : TI(0);
-                }
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu)
-#pragma unroll
-                  for (int p = 0; p < 8; ++p) d[p] += double(vv[uu][p]) * double(wv[uu]);
-              }
-            }
-            tm.template tsum<9>(d);
-            if (tid == 0) {
-#pragma unroll
-              for (int q = 0; q < 8; ++q)
-                if (q < nk0) coef[q] = d[q];
-            }
-            for (int k0 = 8; k0 <= j; k0 += 8) {  // remaining dot chunks
-              const int nk = min(j + 1 - k0, 8);
-              tm.bytes = uni(tm.bytes + ((1.0 + nk) * sizeof(TI) * n0));
-#pragma unroll
-              for (int q = 0; q < 9; ++q) d[q] = 0.0;
-              for (int q = tid; q < nb; q += BLOCK) {
-                const int idx = tm.bidx(q);
-                const double wd = double(Vn[idx]);
-#pragma unroll
-                for (int p = 0; p < 8; ++p)
-                  if (p < nk) d[p] += double(tm.V[(k0 + p) * vs + idx]) * wd;
-              }
-              tm.template tsum<9>(d);
-              if (tid == 0) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                  if (q < nk) coef[k0 + q] = d[q];
-              }
-            }
-            // projections onto the normalised basis enter H; V_q is stored with
-            // norm 1/sc[q], so w loses (sc[q]^2 <V_q, w>) V_q
-            if (tid == 0)
-              for (int q = 0; q <= j; ++q) {
-                const double hq = sc[q] * sc[j] * coef[q];
-                H[q * kMaxRestart + j] = (pass ? H[q * kMaxRestart + j] : 0.0) + hq;
-                coef[q] = sc[q] * sc[q] * coef[q];
-              }
-            __syncthreads();
-            STM_T1(t_dot, 3);
-            STM_T0(t_pb);
-            // pass B: V_{j+1} -= sum_q coef_q V_q over the owned nodes; norm
-            nn[0] = 0.0;
-            tm.bytes = uni(tm.bytes + ((j + 3.0) * sizeof(TI) * n0));
-            // The first of two passes with at most 8 basis vectors also forms
-            // the second pass's dots from the values it holds: the same nodes
-            // per thread, the same operations in the same order as the
-            // separate loops, one read of the vectors fewer.
-            const bool fuse = pass + 1 < kPasses && j < 8;
-            if (fuse) {
-#pragma unroll
-              for (int q = 0; q < 9; ++q) dnext[q] = 0.0;
-              for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                double w[2];
-                int ix[2];
-                TI vv[2][8];
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                  const int q = qb + uu * BLOCK;
-                  ix[uu] = q < nb ? tm.bidx(q) : 0;
-                  w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
-#pragma unroll
-                  for (int p = 0; p < 8; ++p) vv[uu][p] = (p <= j && q < nb) ? tm.V[p * vs + ix[uu]] : TI(0);
-                }
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                  const double cq = p <= j ? coef[p] : 0.0;
-#pragma unroll
-                  for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[uu][p]);
-                }
-                TI wt[2];
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                  wt[uu] = TI(0);
-                  if (qb + uu * BLOCK < nb) {
-                    wt[uu] = TI(w[uu]);
-                    Vn[ix[uu]] = wt[uu];
-                  }
-                }
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu)
-#pragma unroll
-                  for (int p = 0; p < 8; ++p) dnext[p] += double(vv[uu][p]) * double(wt[uu]);
-              }
-            } else {
-              // vectors in chunks of 4, all loads of a chunk issued before use
-              for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                double w[2];
-                int ix[2];
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                  const int q = qb + uu * BLOCK;
-                  ix[uu] = q < nb ? tm.bidx(q) : 0;
-                  w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
-                }
-                for (int q0 = 0; q0 <= j; q0 += 4) {
-                  TI vv[4][2];
-#pragma unroll
-                  for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int uu = 0; uu < 2; ++uu)
-                      vv[p][uu] = (q0 + p <= j) ? tm.V[(q0 + p) * vs + ix[uu]] : TI(0);
-#pragma unroll
-                  for (int p = 0; p < 4; ++p) {
-                    const double cq = (q0 + p <= j) ? coef[q0 + p] : 0.0;
-#pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[p][uu]);
-                  }
-                }
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                  if (qb + uu * BLOCK < nb) {
-                    const TI wt = TI(w[uu]);
-                    Vn[ix[uu]] = wt;
-                    nn[0] += double(wt) * double(wt);
-                  }
-                }
-              }
-            }
-            // Only the last pass's norm is used.  A member reads V_{j+1} at
-            // its own nodes only, and in the same thread-to-node order as it
-            // wrote them, so the first pass ends with a workgroup barrier.
-            have_dots = fuse;
-            if (pass + 1 < kPasses)
-              __syncthreads();
-            else
-              tm.template tsum<1>(nn);
-            STM_T1(t_pb, 4);
-          }
-          const double hn = uni(sqrt(nn[0]));
-          if (tid == 0) {
-            const double hj1 = sc[j] * hn;
-            sc[j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
-            for (int q = 0; q < j; ++q) {  // previous rotations on column j
-              const double a = H[q * kMaxRestart + j], b = H[(q + 1) * kMaxRestart + j];
-              H[q * kMaxRestart + j] = cs_[q] * a + sn_[q] * b;
-              H[(q + 1) * kMaxRestart + j] = -sn_[q] * a + cs_[q] * b;
-            }
-            const double a = H[j * kMaxRestart + j];
-            const double r = sqrt(a * a + hj1 * hj1);
-            const double c = r > 0.0 ? a / r : 1.0, sn = r > 0.0 ? hj1 / r : 0.0;
-            cs_[j] = c;
-            sn_[j] = sn;
-            H[j * kMaxRestart + j] = r;
-            H[(j + 1) * kMaxRestart + j] = 0.0;
-            gv[j + 1] = -sn * gv[j];
-            gv[j] = c * gv[j];
-            sh_resid = fabs(gv[j + 1]);
-          }
-          __syncthreads();
-          jdim = j + 1;
-          const double resid = uni(sh_resid);
-          if (!(resid > tol_abs) || !(hn > 0.0)) break;
-        }
-        krylov_total += jdim;
-        if (tid == 0) {
-          for (int q = jdim - 1; q >= 0; --q) {
-            double acc = gv[q];
-            for (int p = q + 1; p < jdim; ++p) acc -= H[q * kMaxRestart + p] * yv[p];
-            yv[q] = acc / H[q * kMaxRestart + q];
-          }
-          for (int q = 0; q < jdim; ++q) coef[q] = yv[q] * sc[q];
-        }
-        __syncthreads();
-        // ---- u += sum_q y_q z_q (float64) over the owned nodes, max-norm of the step ----
-        STM_T0(t_up);
-        double dm = 0.0;
-        tm.bytes = uni(tm.bytes + (double(jdim) * sizeof(TI) * n0 + 24.0 * n0));
-        for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-          double dl[2] = {0.0, 0.0}, uo[2];
-          int ix[2];
-#pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            const int q = qb + v * BLOCK;
-            ix[v] = q < nb ? tm.bidx(q) : 0;
-            uo[v] = q < nb ? u[ix[v]] : 0.0;
-          }
-          for (int q0 = 0; q0 < jdim; q0 += 4) {
-            TI zz[4][2];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-              for (int v = 0; v < 2; ++v) zz[p][v] = (q0 + p < jdim) ? tm.Z[(q0 + p) * vs + ix[v]] : TI(0);
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-              const double cq = (q0 + p < jdim) ? coef[q0 + p] : 0.0;
-#pragma unroll
-              for (int v = 0; v < 2; ++v) dl[v] += cq * double(zz[p][v]);
-            }
-          }
-#pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            if (qb + v * BLOCK < nb) {
-              u[ix[v]] = uo[v] + dl[v];
-              dlt[ix[v]] = dl[v];
-              dm = fmax(dm, fabs(dl[v]));
-            }
-          }
-        }
-        dmax = uni(tm.tmax(dm));  // its barrier also publishes u to the other members
-        STM_T1(t_up, 5);
-        const double ach = sh_resid / beta;
+        // ---- Newton step by GMRES ----
+        io.beta = beta;
+        io.eta = eta;
+        io.model_bytes = model_bytes;
+        do_step<kStepGmres>(tm, io, &calls, smem_dyn, red, omega_tab);
+        krylov_total += io.jdim;
+        model_bytes = uni(io.model_bytes);
+        dmax = uni(io.dmax);
+        const double ach = io.resid / beta;
         if (!isfinite(dmax)) {
           status = -5;
           break;
@@ -2334,6 +2649,7 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
   tm.part = task.part;
   tm.fault = task.fault;
   tm.gen = 0;
+  tm.hgen = 0;
   tm.rslot = 0;
   tm.broken = false;
 #ifdef STM_PHASE_TIMERS
@@ -2397,7 +2713,7 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
         if (MG) tm.coarse_weights(U + (int64_t)k * n0, inv_dt);
         const TI* b = r + k * vs;
         if (k > 0) {
-          tm.template staged<TI>(
+          tm.template staged<TI, 0>(
               0, z + (k - 1) * vs, r + k * vs, (const TI*)nullptr, (const TI*)nullptr,
               KScale<TI>{TI(1.0 - th)}, [c0 = TI(-inv_dt)](TI a, TI) { return c0 * a; },
               [&](int idx, int, int, int, TI y, TI, TI ro, TI, TI) { gmem(gT)[idx] = ro - y; });
@@ -2410,13 +2726,13 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
     auto spmv = [&](const TI* __restrict__ x, TI* __restrict__ y) {
       for (int k = 0; k < m; ++k) {
         TI* yk = y + k * vs;
-        tm.template staged<TI>(
+        tm.template staged<TI, 0>(
             0, x + k * vs, gW + k * vs, (const TI*)nullptr, (const TI*)nullptr,
             KScale<TI>{TI(th)}, [](TI a, TI ww) { return ww * a; },
             [&](int idx, int, int, int, TI v, TI, TI, TI, TI) { gmem(yk)[idx] = v; });
         if (k > 0)
           // in place: f1 = y_k enters only the body (its own node), never the element terms
-          tm.template staged<TI>(
+          tm.template staged<TI, 0>(
               0, x + (k - 1) * vs, yk, (const TI*)nullptr, (const TI*)nullptr,
               KScale<TI>{TI(1.0 - th)}, [c0 = TI(-inv_dt)](TI a, TI) { return c0 * a; },
               [&](int idx, int, int, int, TI v, TI, TI yo, TI, TI) { gmem(yk)[idx] = yo + v; });
@@ -2447,7 +2763,7 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
         TI* Vk = gV + k * vs;
         TI* wk = gW + k * vs;
         TI* dk = gD + k * vs;
-        tm.template staged<double>(
+        tm.template staged<double, 1>(
             0, uk, up, tm.kdiag0, (const double*)nullptr,
             [th](double a, double b) { return th * a + (1.0 - th) * b; },
             [&](double a, double b) { return (a - b) * inv_dt - react(a, kr, ar); },
