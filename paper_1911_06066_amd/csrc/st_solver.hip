@@ -804,196 +804,140 @@ struct Team {
   __device__ __forceinline__ void staged_tiles(int l, const T* __restrict__ f0, const T* __restrict__ f1,
                                                const T* __restrict__ f2, const T* __restrict__ f3, KV kval, MV mval,
                                                Body body) const {
-    constexpr int NV = (DIM == 3) ? 8 : 4;
-    constexpr int U = 4;                      // batched loads per thread in the staging loop
-    constexpr int UA = (DIM == 3) ? 1 : 2;    // independent elements per thread in phase A
-    const GridDev& g = L->g[l];
+    static_assert(DIM == 2, "the tiled pass is 2D");
+    constexpr int NV = 4;
+    constexpr int U = 4;   // batched loads per thread in the staging loop
+    constexpr int UA = 2;  // independent elements per thread in phase A
+    const STM_CONST LevelDev* __restrict__ Lp = cmem(here(L));
+    const STM_CONST GridDev& g = Lp->g[l];
     const int nx = g.nx, EX = g.ex;
     const unsigned mnx = g.mnx, mex = g.mex;
     const int nf = 2 + (f2 ? 1 : 0) + (f3 ? 1 : 0);
-    const int Ry = L->tile_y[l][sizeof(T) == 8 ? 0 : 1][nf - 2];
-    const int Rz = (DIM == 3) ? L->tile_z[l][sizeof(T) == 8 ? 0 : 1][nf - 2] : 1;
-    const int nzz = (DIM == 3) ? g.nz : 1;
+    const int Ry = Lp->tile_y[l][sizeof(T) == 8 ? 0 : 1][nf - 2];
     const int jb0 = l == 0 ? this->jb0 : 0, jb1 = l == 0 ? this->jb1 : g.ny;
     const double* __restrict__ sg = mgS(l);
-    const double* __restrict__ fib = L->fib[l];
+    const double* __restrict__ fib = Lp->fib[l];
     const double tau = prm.tau, zr = prm.zr;
-    const T hx = T(g.hx), hy = T(g.hy), hz = T(g.hz);
-    const T cxx = (DIM == 3) ? hy * hz / (T(36) * hx) : hy / (T(6) * hx);
-    const T cyy = (DIM == 3) ? hx * hz / (T(36) * hy) : hx / (T(6) * hy);
-    const T czz = hx * hy / (T(36) * hz), cxy = hz / T(24);
-    const T cm = (DIM == 3) ? hx * hy * hz / T(216) : hx * hy / T(36);
-    for (int k0 = 0; k0 < nzz; k0 += Rz) {
-      for (int j0 = jb0; j0 < jb1; j0 += Ry) {
-        const int je = min(j0 + Ry, jb1);  // computed rows [j0, je)
-        const int ke = min(k0 + Rz, nzz);  // computed planes [k0, ke)
-        const int jr0 = max(j0 - 1, 0), jr1 = min(je, g.ny - 1);
-        const int kr0 = (DIM == 3) ? max(k0 - 1, 0) : 0, kr1 = (DIM == 3) ? min(ke, g.nz - 1) : 0;
-        const int sy = jr1 - jr0 + 1;
-        const int lay = sy * nx;  // staged nodes per plane
-        const int nst = lay * (kr1 - kr0 + 1);
-        const int ey0 = max(j0 - 1, 0), ey1 = min(je - 1, g.ey - 1);
-        const int ez0 = (DIM == 3) ? max(k0 - 1, 0) : 0, ez1 = (DIM == 3) ? min(ke - 1, g.ez - 1) : 0;
-        const int sey = ey1 - ey0 + 1;
-        const int elay = sey * EX;  // staged elements per plane
-        const int nse = elay * (ez1 - ez0 + 1);
-        const int nfr = (DIM == 3) ? (ez1 - ez0 + 1) : sey;  // fibre rows
-        const int fr0 = (DIM == 3) ? ez0 : ey0;
-        const unsigned mlay = (DIM == 3) ? fdiv_magic((unsigned)lay) : 0u;
-        const unsigned melay = (DIM == 3) ? fdiv_magic((unsigned)elay) : 0u;
-        T* l0 = reinterpret_cast<T*>(smem);
-        T* l1 = l0 + nst;
-        T* l2 = l1 + nst;
-        T* l3 = l2 + (f2 ? nst : 0);
-        double* ls = reinterpret_cast<double*>(smem + ((nf * (size_t)nst * sizeof(T) + 15) & ~(size_t)15));
-        T* lc = reinterpret_cast<T*>(ls + nse);  // [NV][nse]
-        double* lf = reinterpret_cast<double*>(
-            reinterpret_cast<unsigned char*>(lc) + ((NV * (size_t)nse * sizeof(T) + 15) & ~(size_t)15));
-        // ---- stage: batched loads, then LDS stores ----
-        STM_T0(t_st);
-        const int gq0 = (DIM == 3) ? (kr0 * g.ny + jr0) * nx : jr0 * nx;
-        const int plane = g.ny * nx;
-        for (int qb = threadIdx.x; qb < nst; qb += BLOCK * U) {
-          T r0[U], r1[U], r2[U], r3[U];
+    const T hx = T(g.hx), hy = T(g.hy);
+    const T cxx = hy / (T(6) * hx), cyy = hx / (T(6) * hy), cm = hx * hy / T(36);
+    for (int j0 = jb0; j0 < jb1; j0 += Ry) {
+      const int je = min(j0 + Ry, jb1);  // computed rows [j0, je)
+      const int jr0 = max(j0 - 1, 0), jr1 = min(je, g.ny - 1);
+      const int nst = (jr1 - jr0 + 1) * nx;  // staged nodes
+      const int ey0 = max(j0 - 1, 0), ey1 = min(je - 1, g.ey - 1);
+      const int sey = ey1 - ey0 + 1;
+      const int nse = sey * EX;  // staged elements
+      T* l0 = reinterpret_cast<T*>(smem);
+      T* l1 = l0 + nst;
+      T* l2 = l1 + nst;
+      T* l3 = l2 + (f2 ? nst : 0);
+      double* ls = reinterpret_cast<double*>(smem + ((nf * (size_t)nst * sizeof(T) + 15) & ~(size_t)15));
+      T* lc = reinterpret_cast<T*>(ls + nse);  // [NV][nse]
+      double* lf = reinterpret_cast<double*>(
+          reinterpret_cast<unsigned char*>(lc) + ((NV * (size_t)nse * sizeof(T) + 15) & ~(size_t)15));
+      // ---- stage: batched loads, then LDS stores ----
+      STM_T0(t_st);
+      const int gq0 = jr0 * nx;
+      for (int qb = threadIdx.x; qb < nst; qb += BLOCK * U) {
+        T r0[U], r1[U], r2[U], r3[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int q = qb + u * BLOCK;
-            if (q < nst) {
-              int gq;
-              if constexpr (DIM == 3) {
-                const int lz = fdiv(q, mlay);
-                gq = gq0 + lz * plane + (q - lz * lay);
-              } else {
-                gq = gq0 + q;
-              }
-              r0[u] = f0[gq];
-              r1[u] = f1[gq];
-              if (f2) r2[u] = f2[gq];
-              if (f3) r3[u] = f3[gq];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int q = qb + u * BLOCK;
-            if (q < nst) {
-              l0[q] = r0[u];
-              l1[q] = r1[u];
-              if (f2) l2[q] = r2[u];
-              if (f3) l3[q] = r3[u];
-            }
+        for (int u = 0; u < U; ++u) {
+          const int q = qb + u * BLOCK;
+          if (q < nst) {
+            r0[u] = f0[gq0 + q];
+            r1[u] = f1[gq0 + q];
+            if (f2) r2[u] = f2[gq0 + q];
+            if (f3) r3[u] = f3[gq0 + q];
           }
         }
-        {
-          const int ge0 = (DIM == 3) ? (ez0 * g.ey + ey0) * EX : ey0 * EX;
-          const int eplane = g.ey * EX;
-          for (int qb = threadIdx.x; qb < nse; qb += BLOCK * U) {
-            double rs[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const int q = qb + u * BLOCK;
-              if (q < nse) {
-                int ge;
-                if constexpr (DIM == 3) {
-                  const int lz = fdiv(q, melay);
-                  ge = ge0 + lz * eplane + (q - lz * elay);
-                } else {
-                  ge = ge0 + q;
-                }
-                rs[u] = sg[ge];
-              }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const int q = qb + u * BLOCK;
-              if (q < nse) ls[q] = rs[u];
-            }
-          }
-          for (int q = threadIdx.x; q < kFibStride * nfr; q += BLOCK) lf[q] = fib[kFibStride * fr0 + q];
-        }
-        __syncthreads();
-        STM_T1P(t_st, 6);
-        STM_T0(t_pa);
-        // ---- phase A: element contributions (UA elements per iteration) ----
-        for (int qb = threadIdx.x; qb < nse; qb += UA * BLOCK) {
-          T kv[UA][NV], mv[UA][NV], out[UA][NV];
-          typename TensorOf<T, DIM>::type D[UA];
-#pragma unroll
-          for (int h = 0; h < UA; ++h) {
-            const int q = qb + h * BLOCK;
-            const int qq = q < nse ? q : 0;
-            int lz = 0, rem = qq;
-            if constexpr (DIM == 3) {
-              lz = fdiv(qq, melay);
-              rem = qq - lz * elay;
-            }
-            const int r = fdiv(rem, mex);
-            const int ex = rem - r * EX;
-            const int ey = ey0 + r, ez = ez0 + lz;
-            D[h] = tensor_from<T, DIM>(ls[qq], lf + kFibStride * ((DIM == 3) ? lz : r), tau, zr);
-            const int base = ((ez - kr0) * sy + (ey - jr0)) * nx + ex;
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-              const int o = base + ((v >> 2) & 1) * lay + ((v >> 1) & 1) * nx + (v & 1);
-              const T a = l0[o], b = l1[o];
-              kv[h][v] = kval(a, b);
-              mv[h][v] = mval(a, b);
-            }
-          }
-#pragma unroll
-          for (int h = 0; h < UA; ++h) {
-            elem_apply_2d<T>(kv[h], mv[h], D[h], cxx, cyy, cm, out[h]);
-          }
-#pragma unroll
-          for (int h = 0; h < UA; ++h) {
-            const int q = qb + h * BLOCK;
-            if (q < nse) {
-#pragma unroll
-              for (int v = 0; v < NV; ++v) lc[v * nse + q] = out[h][v];
-            }
+        for (int u = 0; u < U; ++u) {
+          const int q = qb + u * BLOCK;
+          if (q < nst) {
+            l0[q] = r0[u];
+            l1[q] = r1[u];
+            if (f2) l2[q] = r2[u];
+            if (f3) l3[q] = r3[u];
           }
         }
-        __syncthreads();
-        STM_T1P(t_pa, 7);
-        // ---- phase B: nodes of the tile ----
-        const int cy = je - j0;
-        const int clay = cy * nx;
-        const int nc = clay * (ke - k0);
-        const unsigned mclay = (DIM == 3) ? fdiv_magic((unsigned)clay) : 0u;
-        for (int q = threadIdx.x; q < nc; q += BLOCK) {
-          int lz = 0, rem = q;
-          if constexpr (DIM == 3) {
-            lz = fdiv(q, mclay);
-            rem = q - lz * clay;
-          }
-          const int r = fdiv(rem, mnx);
-          const int i = rem - r * nx;
-          const int j = j0 + r, k = k0 + lz;
-          const int idx = (DIM == 3) ? ((k * g.ny + j) * nx + i) : (j * nx + i);
-          T y = T(0);
-#pragma unroll
-          for (int c = 0; c < ((DIM == 3) ? 2 : 1); ++c) {
-            const int ez = k - 1 + c;
-            const bool okz = (DIM == 2) || (ez >= 0 && ez < g.ez);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              const int ey = j - 1 + b;
-              const bool oky = okz && ey >= 0 && ey < g.ey;
-#pragma unroll
-              for (int a = 0; a < 2; ++a) {
-                const int ex = i - 1 + a;
-                const bool ok = oky && ex >= 0 && ex < EX;
-                const int el = (((DIM == 3) ? (ez - ez0) : 0) * sey + (ey - ey0)) * EX + ex;
-                const int v = (1 - a) + 2 * (1 - b) + ((DIM == 3) ? 4 * (1 - c) : 0);
-                const T cv = lc[v * nse + (ok ? el : 0)];
-                y += ok ? cv : T(0);
-              }
-            }
-          }
-          const int o = (((DIM == 3) ? (k - kr0) : 0) * sy + (j - jr0)) * nx + i;
-          body(NodeAt{0, (unsigned)idx}, i, j, k, y, l0[o], l1[o], f2 ? l2[o] : T(0), f3 ? l3[o] : T(0));
-        }
-        __syncthreads();
       }
+      {
+        const int ge0 = ey0 * EX;
+        for (int qb = threadIdx.x; qb < nse; qb += BLOCK * U) {
+          double rs[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int q = qb + u * BLOCK;
+            if (q < nse) rs[u] = sg[ge0 + q];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int q = qb + u * BLOCK;
+            if (q < nse) ls[q] = rs[u];
+          }
+        }
+        for (int q = threadIdx.x; q < kFibStride * sey; q += BLOCK) lf[q] = fib[kFibStride * ey0 + q];
+      }
+      __syncthreads();
+      STM_T1P(t_st, 6);
+      STM_T0(t_pa);
+      // ---- phase A: element contributions (UA elements per iteration) ----
+      for (int qb = threadIdx.x; qb < nse; qb += UA * BLOCK) {
+        T kv[UA][NV], mv[UA][NV], out[UA][NV];
+        Tensor2<T> D[UA];
+#pragma unroll
+        for (int h = 0; h < UA; ++h) {
+          const int q = qb + h * BLOCK;
+          const int qq = q < nse ? q : 0;
+          const int r = fdiv(qq, mex);
+          D[h] = tensor_from<T, 2>(ls[qq], lf + kFibStride * r, tau, zr);
+          const int base = (ey0 + r - jr0) * nx + (qq - r * EX);
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            const int o = base + ((v >> 1) & 1) * nx + (v & 1);
+            const T a = l0[o], b = l1[o];
+            kv[h][v] = kval(a, b);
+            mv[h][v] = mval(a, b);
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < UA; ++h) elem_apply_2d<T>(kv[h], mv[h], D[h], cxx, cyy, cm, out[h]);
+#pragma unroll
+        for (int h = 0; h < UA; ++h) {
+          const int q = qb + h * BLOCK;
+          if (q < nse) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) lc[v * nse + q] = out[h][v];
+          }
+        }
+      }
+      __syncthreads();
+      STM_T1P(t_pa, 7);
+      // ---- phase B: nodes of the tile ----
+      const int nc = (je - j0) * nx;
+      for (int q = threadIdx.x; q < nc; q += BLOCK) {
+        const int r = fdiv(q, mnx);
+        const int i = q - r * nx;
+        const int j = j0 + r;
+        T y = T(0);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int ey = j - 1 + b;
+          const bool oky = ey >= 0 && ey < g.ey;
+#pragma unroll
+          for (int a = 0; a < 2; ++a) {
+            const int ex = i - 1 + a;
+            const bool ok = oky && ex >= 0 && ex < EX;
+            const int el = (ey - ey0) * EX + ex;
+            const int v = (1 - a) + 2 * (1 - b);
+            const T cv = lc[v * nse + (ok ? el : 0)];
+            y += ok ? cv : T(0);
+          }
+        }
+        const int o = (j - jr0) * nx + i;
+        body(NodeAt{j0 * nx, (unsigned)q}, i, j, 0, y, l0[o], l1[o], f2 ? l2[o] : T(0), f3 ? l3[o] : T(0));
+      }
+      __syncthreads();
     }
   }
 
@@ -1536,9 +1480,8 @@ struct Team {
     __syncthreads();
   }
 
-  // weight of sweep s (0-based) of grid l
+  // weight of sweep s (0-based) of grid l (the fixed weight fills the table at the kernel's start)
   __device__ __forceinline__ TI wgt(int l, int s) const {
-    if (prm.smoother == 0) return TI(prm.smooth_omega);
     return TI(omega[l * kMaxSweeps + s]);
   }
 
@@ -2219,6 +2162,8 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
   const TeamTask task = tasks[blockIdx.x];
   const LevelDev* L = levels + task.level;
   const int tid = threadIdx.x;
+  for (int q = tid; q < kMaxMG * kMaxSweeps; q += BLOCK) omega_tab[q] = prm.smooth_omega;
+  __syncthreads();
 
   Team<TI, DIM, BLOCK, MG> tm;
   tm.L = L;
@@ -2634,6 +2579,8 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
   const TeamTask task = tasks[blockIdx.x];
   const LevelDev* L = levels + task.level;
   const int tid = threadIdx.x;
+  for (int q = tid; q < kMaxMG * kMaxSweeps; q += BLOCK) omega_tab[q] = prm.smooth_omega;
+  __syncthreads();
 
   Team<TI, DIM, BLOCK, MG> tm;
   tm.L = L;

@@ -44,6 +44,8 @@ CASES = [
     dict(shape=(17, 17), m=8, S=2, precision="fp64", G=1, sigma_f0=0.2),
     # fixed weights: GMRES only
     dict(shape=(17, 17), m=8, S=2, precision="fp64", G=1, smoother=1),
+    dict(shape=(9, 9, 5), m=8, S=2, precision="fp64", G=1, smoother=1, smooth_omega=0.4),
+    dict(shape=(9, 9, 9), m=8, S=2, precision="mixed", G=4, smoother=1, smooth_omega=0.4),
     # corrections do not count against the Newton limit
     dict(shape=(17, 17), m=32, S=2, precision="fp64", G=1, newton_max=2),
 ]
@@ -65,7 +67,7 @@ def test_defect_corrections_match_oracle(torch_dev, c):
         over["max_lanes"] = c["lanes"]
     if "tuning" in c:
         over["level_tuning"] = [c["tuning"]]
-    for k in ("smoother", "newton_max"):
+    for k in ("smoother", "smooth_omega", "newton_max"):
         if k in c:
             over[k] = c[k]
     with Context(wl, **over) as ctx:
