@@ -424,15 +424,11 @@ struct Team {
   }
 
   // ---- owned nodes of grid 0 ----------------------------------------------
-  // Rows per tile of a z-marching pass on grid l with fields of fbytes bytes:
-  // the LDS budget (set on the host) and the per-thread element and output-node
-  // columns.
-  static constexpr int kCE = BLOCK == 1024 ? 2 : 3, kCB = kCE;
+  static constexpr int kCE = march_columns(BLOCK), kCB = kCE;
   template <typename LP>
   __device__ __forceinline__ int zrows_max(LP Lp, int l, int fbytes) const {
     const auto& g = Lp->g[l];
-    return max(1, min((int)Lp->tile_y[l][fbytes == 8 ? 0 : 1][0],
-                      min(kCE * BLOCK / g.ex - 1, kCB * BLOCK / g.nx)));
+    return march_rows(g.nx, g.ex, Lp->tile_y[l][fbytes == 8 ? 0 : 1][0], BLOCK);
   }
   // A member owns node rows [jb0, jb1) of planes [kb0, kb1) (3D), q-th in
   // plane-major order.
@@ -451,29 +447,14 @@ struct Team {
       return ((kb0 + kk) * g.ny + jb0) * g.nx + (q - kk * w);
     }
   }
-  // The member's box of grid 0: in 3D the G members are split into Gz
-  // groups of planes and each group into G / Gz bands of rows (a z-step of a
-  // pass then carries more nodes than with bands of rows alone).
+  // The member's box of grid 0 (team_groups; the host launches only team sizes
+  // that it divides).
   __device__ __forceinline__ void set_box() {
     const GridDev& g = L->g[0];
     int Gz = 1;
     if constexpr (DIM == 3) {
-      // Gz minimises the z-steps of a member's pass: tiles x (planes + the
-      // step on the layer below in every group but the first + about two steps
-      // of prologue), every member keeping at least 4 planes (less one where the
-      // groups' steps are evened out)
-      const int Rmax = zrows_max(L, 0, sizeof(TI));
-      int best = -1;
-      for (int d = 1; d <= G; ++d) {
-        if (G % d != 0 || g.nz < 4 * d) continue;
-        const int Gy = G / d;
-        const int rows = (g.ny + Gy - 1) / Gy, steps = (g.nz + d - 1 + d - 1) / d;
-        const int cost = ((rows + Rmax - 1) / Rmax) * (steps + 2);
-        if (best < 0 || cost < best) {
-          best = cost;
-          Gz = d;
-        }
-      }
+      int cost;
+      Gz = max(1, team_groups(3, g.ny, g.nz, zrows_max(L, 0, sizeof(TI)), G, &cost));
     }
     const int Gy = G / Gz, ry = rank / Gz, rz = rank - ry * Gz;
     gy = Gy;
@@ -1727,7 +1708,7 @@ struct Team {
           node_ref(V0, at) = TI(r);
           node_ref(w0, at) = TI(w);
           node_ref(di, at) = dd;
-          if constexpr (DIM == 3 && !MG) {
+          if constexpr (!MG) {
             if (x1) node_ref(x1, at) = om1 * TI(r) * dd;
           }
           rr[0] += r * r;

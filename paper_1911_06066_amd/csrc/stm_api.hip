@@ -374,10 +374,7 @@ stm_status build_level(stm_ctx* c, int l, LevelHost& out) {
         by = ry;
       }
       if (by == 0) return fail(c, STM_E_UNSUPPORTED, "grid row too wide for the LDS staging budget");
-      for (int nfl = 2; nfl <= 4; ++nfl) {
-        d.tile_y[k][es][nfl - 2] = by;
-        d.tile_z[k][es][nfl - 2] = 1;
-      }
+      for (int nfl = 2; nfl <= 4; ++nfl) d.tile_y[k][es][nfl - 2] = by;
     }
   }
   for (int k = 0; k < nmg && p.dim == 2; ++k) {
@@ -385,31 +382,18 @@ stm_status build_level(stm_ctx* c, int l, LevelHost& out) {
     for (int es = 0; es < 2; ++es) {
       const size_t fb = es == 0 ? 8 : 4;
       for (int nfl = 2; nfl <= 4; ++nfl) {
-        int by = 1, bz = 1;
-        double best = -1.0;
-        const int zmax = p.dim == 3 ? gk.nz : 1;
-        for (int rz = 1; rz <= zmax; ++rz) {
-          for (int ry = 1; ry <= gk.ny; ++ry) {
-            const int sy = std::min(ry + 2, gk.ny), sz = p.dim == 3 ? std::min(rz + 2, gk.nz) : 1;
-            const int ey = std::min(ry + 1, gk.ey), ez = p.dim == 3 ? std::min(rz + 1, gk.ez) : 1;
-            const size_t nv = p.dim == 3 ? 8 : 4;  // per-element vertex contributions
-            // staged nodal fields, element conductivities, element
-            // contributions, fibre rows of the tile
-            const size_t bytes = nfl * fb * (size_t)sy * sz * gk.nx + 16 +
-                                 (8 + fb * nv) * (size_t)ey * ez * gk.ex + 16 +
-                                 8 * kFibStride * (size_t)(p.dim == 2 ? ey : ez);
-            if (bytes > budget) break;
-            const double eff = (double)std::min(ry, gk.ny) * std::min(rz, zmax) / ((double)sy * sz) + 1e-6 * ry * rz;
-            if (eff > best) {
-              best = eff;
-              by = ry;
-              bz = rz;
-            }
-          }
+        int by = 0;
+        for (int ry = 1; ry <= gk.ny; ++ry) {
+          const int sy = std::min(ry + 2, gk.ny), ey = std::min(ry + 1, gk.ey);
+          // staged nodal fields, element conductivities, element
+          // contributions, fibre rows of the tile
+          const size_t bytes = nfl * fb * (size_t)sy * gk.nx + 16 + (8 + fb * 4) * (size_t)ey * gk.ex + 16 +
+                               8 * kFibStride * (size_t)ey;
+          if (bytes > budget) break;
+          by = ry;
         }
-        if (best < 0) return fail(c, STM_E_UNSUPPORTED, "grid row too wide for the LDS staging budget");
+        if (by == 0) return fail(c, STM_E_UNSUPPORTED, "grid row too wide for the LDS staging budget");
         d.tile_y[k][es][nfl - 2] = by;
-        d.tile_z[k][es][nfl - 2] = bz;
       }
     }
   }
@@ -570,12 +554,41 @@ stm_status run_tasks(stm_ctx* c, std::vector<TeamTask>& teams, int block, const 
   return STM_OK;
 }
 
-// Largest team size a level allows: single-grid V-cycle and >= 3 node rows per member
-// (a member's staged tiles carry one halo row on each side).
-int max_team(const stm_ctx* c, int level) {
+// Cost of a pass on a member of a team of G on the level's grid (team_groups);
+// 0 where the grid has no such division or a V-cycle, which takes teams of one.
+int team_cost(const stm_ctx* c, int level, int G) {
   const LevelDev& d = c->levels[level].dev;
-  if (d.nmg > 1) return 1;
-  return std::max(1, std::min(kMaxTeam, d.g[0].ny / 3));
+  const GridDev& g = d.g[0];
+  if (d.nmg > 1 && G > 1) return 0;
+  const int block = auto_block(c->p, g.n, c->any_mg);
+  int cost;
+  const int rows = march_rows(g.nx, g.ex, d.tile_y[0][c->inner_fp32 ? 1 : 0][0], block);
+  return team_groups(c->p.dim, g.ny, g.nz, rows, G, &cost) ? cost : 0;
+}
+
+// Largest team of at most `limit` workgroups that divides the level's grid.
+int max_team(const stm_ctx* c, int level, int limit = kMaxTeam) {
+  int G = std::min(kMaxTeam, limit);
+  while (G > 1 && team_cost(c, level, G) == 0) --G;
+  return std::max(1, G);
+}
+
+// The team of at most `limit` workgroups with the cheapest pass, the largest of
+// several: a 3D grid's passes depend on how the members divide into planes and
+// rows and not on their number alone.  16 samples of 41^3 nodes (float64, 24
+// steps): 60.8 ms with teams of 13, which divide into rows only, 23.8 with 12
+// and 21.4 with 16.  Of equal passes the larger team's have fewer rows: 8 samples
+// of 129x129x33 (float32 corrections, 16 steps) 60.8 ms with 24, 56.6 with 32.
+int best_team(const stm_ctx* c, int level, int limit) {
+  int best = 1, low = team_cost(c, level, 1);
+  for (int G = 2; G <= max_team(c, level, limit); ++G) {
+    const int cost = team_cost(c, level, G);
+    if (cost > 0 && cost <= low) {
+      low = cost;
+      best = G;
+    }
+  }
+  return best;
 }
 
 // Workgroups that can be resident at once for the solver configuration.
@@ -780,8 +793,8 @@ stm_status st_solve_impl(stm_ctx* c, int level, const double* sigma, const doubl
   const int cap = std::min(c->p.max_lanes, block_capacity(c, block));
   // few samples: several workgroups per sample (up to the level's limit)
   int G = 1;
-  if (c->p.team_size > 0) G = std::min(c->p.team_size, max_team(c, level));
-  else if (S * 2 <= cap) G = std::min(max_team(c, level), std::max(1, cap / S));
+  if (c->p.team_size > 0) G = max_team(c, level, c->p.team_size);
+  else if (S * 2 <= cap) G = best_team(c, level, cap / S);
   int lanes = std::max(1, std::min(S, cap / G));
   unsigned char* work = nullptr;
   SampleStatsDev* d_stats = nullptr;
@@ -795,6 +808,7 @@ stm_status st_solve_impl(stm_ctx* c, int level, const double* sigma, const doubl
              (size_t)ln * (size_t)L.team_bytes;
     };
     while (lanes > 1 && need(lanes) > kNoAllocBytes) --lanes;
+    while (G > 1 && need(lanes) > kNoAllocBytes) G = max_team(c, level, G - 1);
     if (need(lanes) > kNoAllocBytes)
       return fail(c, STM_E_INVALID,
                   "stm_st_solve_noalloc needs " + std::to_string(need(lanes)) + " bytes of scratch for " +
@@ -952,12 +966,16 @@ struct Group {          // all fine or all coarse members of one MLMC level
 // known; the rest come from t(G) = t1 (a + (1 - a) / G), the part a of a
 // sample's time that does not shrink with the team (synchronisation, per-pass
 // overheads) fitted to the two measured sizes furthest apart, a = 0.15
-// without two, and t1 from the static model without any.
+// without two, and t1 from the static model without any.  Not taken are sizes
+// that do not divide the grid and, unless measured, those with more members
+// than a third of the rows (the estimate is too far from the measured sizes
+// there: a four-level 3D estimate took 91 ms with them, 79 without) and those
+// whose pass is no cheaper than a smaller team's (13 members on 41^3 nodes).
 void team_times(const stm_ctx* c, int l, int gmax, double* t) {
   const LevelDev& d = c->levels[l].dev;
   int g0 = 0, g1 = 0;
   for (int g = 1; g <= gmax; ++g)
-    if (c->tsec[l][g] > 0) {
+    if (c->tsec[l][g] > 0 && team_cost(c, l, g)) {
       if (!g0) g0 = g;
       g1 = g;
     }
@@ -971,7 +989,13 @@ void team_times(const stm_ctx* c, int l, int gmax, double* t) {
     if (den != 0.0) a = std::min(1.0, std::max(0.0, (r * p0 - p1) / den));
   }
   if (g0) t1 = c->tsec[l][g0] / shape(a, g0);
-  for (int g = 1; g <= gmax; ++g) t[g] = c->tsec[l][g] > 0 ? c->tsec[l][g] : t1 * shape(a, g);
+  int low = 0;  // cheapest pass of the smaller sizes
+  for (int g = 1; g <= gmax; ++g) {
+    const int cost = team_cost(c, l, g);
+    const bool taken = cost && (g == 1 || (3 * g <= d.g[0].ny && cost < low));
+    t[g] = cost && c->tsec[l][g] > 0 ? c->tsec[l][g] : (taken ? t1 * shape(a, g) : 1e30);
+    if (cost && (low == 0 || cost < low)) low = cost;
+  }
 }
 
 // Team allocation for one persistent launch: the smallest makespan target T

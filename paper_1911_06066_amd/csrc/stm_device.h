@@ -69,10 +69,9 @@ struct LevelDev {
   int64_t off_gZ;                                       // [m][vs] preconditioned vector / Newton step
   int64_t off_gT;                                       // [vs] forward-substitution right-hand side
   int64_t team_bytes;
-  // LDS tiles of the stencil passes on every grid: node rows (y) and planes
-  // (z) per tile, [grid][8-byte (0) or 4-byte (1) fields][2, 3 or 4 staged
-  // nodal fields]
-  int tile_y[kMaxMG][2][3], tile_z[kMaxMG][2][3];
+  // LDS tiles of the stencil passes on every grid: node rows per tile,
+  // [grid][8-byte (0) or 4-byte (1) fields][2, 3 or 4 staged nodal fields]
+  int tile_y[kMaxMG][2][3];
   // node rows per tile of the fused two-sweep smoother pass (2D), for 8-byte
   // and 4-byte inner vectors
   int tile_p8, tile_p4;
@@ -100,6 +99,42 @@ struct SolverParams {
 };
 
 constexpr int kMaxSweeps = 32;
+
+// Element and output-node columns a thread carries through a z-marching pass (3D).
+__host__ __device__ constexpr int march_columns(int block) { return block == 1024 ? 2 : 3; }
+
+// Rows per tile of a z-marching pass: the LDS budget `lds_rows` and the
+// per-thread columns.
+__host__ __device__ inline int march_rows(int nx, int ex, int lds_rows, int block) {
+  const int c = march_columns(block) * block;
+  const int by_threads = c / ex - 1 < c / nx ? c / ex - 1 : c / nx;
+  const int r = lds_rows < by_threads ? lds_rows : by_threads;
+  return r > 1 ? r : 1;
+}
+
+// How a team of G members divides a grid: in 2D into bands of rows; in 3D into
+// Gz groups of planes and each group into G / Gz bands of rows.  Gz minimises
+// the z-steps of a member's pass, tiles x (planes + the step on the layer below
+// in every group but the first + about two steps of prologue), with at least 3
+// rows and 4 planes (less one where the groups' steps are evened out) per
+// member.  Returns Gz, 0 where there is no such division, and in `cost` the
+// rows (2D) or z-steps (3D) of a pass.
+__host__ __device__ inline int team_groups(int dim, int ny, int nz, int tile_rows, int G, int* cost) {
+  int Gz = 0;
+  *cost = 0;
+  for (int d = 1; d <= (dim == 3 ? G : 1); ++d) {
+    if (G % d != 0 || (d > 1 && nz < 4 * d)) continue;
+    const int Gy = G / d;
+    if (Gy > 1 && ny < 3 * Gy) continue;
+    const int rows = (ny + Gy - 1) / Gy, steps = (nz + d - 1 + d - 1) / d;
+    const int c = dim == 3 ? ((rows + tile_rows - 1) / tile_rows) * (steps + 2) : rows + (G > 1 ? 2 : 0);
+    if (Gz == 0 || c < *cost) {
+      *cost = c;
+      Gz = d;
+    }
+  }
+  return Gz;
+}
 
 // Fibre table: per element row (2D) or layer (3D) the entries (c2, s2, cs) of
 // D_e = (sigma_e c2 + tau s2, sigma_e s2 + tau c2, (sigma_e - tau) cs) in the

@@ -33,6 +33,9 @@ CASES = [
     # 3D, rows split over members, planes split over members
     dict(shape=(9, 9, 5), m=24, S=2, precision="fp64", G=1),
     dict(shape=(9, 9, 17), m=20, S=2, precision="mixed", G=3),
+    # team size from the grid: bands of rows and groups of planes
+    dict(shape=(13, 13, 13), m=8, S=2, precision="fp64", G=0),
+    dict(shape=(9, 7, 9), m=8, S=3, precision="mixed", G=0),
     # smooth initial state: narrower intervals are kept
     dict(shape=(17, 17), m=24, S=2, precision="fp64", G=1, ic_kind="gauss", ic_radius=0.5),
     # the level's own degree and ratio: enough, narrow, and too little to contract
