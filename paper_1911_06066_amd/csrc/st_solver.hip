@@ -454,7 +454,7 @@ struct Team {
     int Gz = 1;
     if constexpr (DIM == 3) {
       int cost;
-      Gz = max(1, team_groups(3, g.ny, g.nz, zrows_max(L, 0, sizeof(TI)), G, &cost));
+      Gz = max(1, team_groups(3, g.nx, g.ny, g.nz, zrows_max(L, 0, sizeof(TI)), G, &cost));
     }
     const int Gy = G / Gz, ry = rank / Gz, rz = rank - ry * Gz;
     gy = Gy;
@@ -1536,6 +1536,259 @@ struct Team {
     }
   }
 
+  // ---- corrections with the stencil in registers (2D) -----------------------
+  // Columns of three nodes per thread: 55 registers each in float64, 28 in
+  // float32, so that nothing spills inside the sweeps at 512 threads.
+  static constexpr int kTriples = sizeof(TI) == 8 ? 3 : 4;
+  // Halo depth of stencil_sweeps, 0 where the member's rows do not fit its
+  // registers or the LDS (jacobi_pair then).  A correction of about 12 sweeps
+  // takes 8.1 us per column a thread holds (3.3 to set up, 0.4 per sweep) and
+  // 1.6 us per exchange, of which there are 12 / h.
+  __device__ __forceinline__ int stencil_halo() const {
+    const STM_CONST LevelDev* __restrict__ Lp = cmem(here(L));
+    const STM_CONST GridDev& g = Lp->g[0];
+    const int rows = (g.ny + G - 1) / G;
+    int best = 0, low = 0;
+    for (int h = 1; h <= (G == 1 ? 1 : min(g.ny / G, 6)); ++h) {
+      const int ext = min(rows + 2 * (h - 1), g.ny);
+      const int cols = ((ext + 2) / 3 * g.nx + BLOCK - 1) / BLOCK;
+      const int words = 2 * ((min(rows + 2 * h, g.ny) + 5) * g.nx + 2) + 1;
+      const int lds = words * (int)sizeof(TI) + (min(ext + 1, g.ey)) * (g.ex + kFibStride) * 8 + 8;
+      if (cols > kTriples || lds > Lp->stage_bytes) break;
+      const int c = 81 * cols + 190 / h;
+      if (!best || c < low) {
+        low = c;
+        best = h;
+      }
+    }
+    return __builtin_amdgcn_readfirstlane(best);
+  }
+  // The sweeps of a defect correction with the scaled operator D^-1 A of every
+  // node in registers: x += om (D^-1 b - D^-1 A x) takes eight products per node
+  // (the diagonal is one), x lies in LDS, and a sweep is one pass with one
+  // barrier, against two passes and barriers and some 60 operations per element
+  // of jacobi_pair, which forms the element products anew in every sweep.  A
+  // thread holds up to kTriples columns of three nodes (15 values of x from LDS
+  // per column instead of 27).  On a team a member computes H - 1 rows beyond
+  // its own on each side, so that x is exchanged with the neighbours once in H
+  // sweeps: after the exchange the staged H rows are right, after each sweep one
+  // less.  The coefficients are formed once per correction from the
+  // conductivities and mass weights staged in LDS; what is left is bound by
+  // latency (loads past a cold L2 after a team barrier, barriers, exchanges).
+  // Per correction, before and after: 33x33 nodes on one workgroup 40 -> 16 us;
+  // 129x129 on teams of 8 95 -> 40; 257x257 in float32 on teams of 16 125 -> 42.  u += x; returns the member's max of |x|.
+  __device__ __forceinline__ double stencil_sweeps(const TI* __restrict__ b, TI* __restrict__ out, int nc, int H,
+                                                   double* __restrict__ u) const {
+    static_assert(DIM == 2, "the sweeps in registers are 2D");
+    using T = TI;
+    const STM_CONST LevelDev* __restrict__ Lp = cmem(here(L));
+    const STM_CONST GridDev& g = Lp->g[0];
+    const int nx = g.nx, ny = g.ny, EX = g.ex, EY = g.ey;
+    const unsigned mnx = g.mnx;
+    bytes = uni(bytes + (4.0 * sizeof(TI) + 16.0) * g.n + dbytes(0));
+    const int e0 = max(jb0 - (H - 1), 0), e1 = min(jb1 + (H - 1), ny);  // computed rows [e0, e1)
+    const int s0 = max(jb0 - H, 0), s1 = min(jb1 + H, ny);              // staged rows [s0, s1)
+    // a row and a node of zeros before the staged rows, four rows and a node after
+    const int pad = nx + 1, total = pad + (s1 - s0 + 4) * nx + 1;
+    const int y0 = max(e0 - 1, 0), y1 = min(e1, EY);  // element rows [y0, y1)
+    T* cur = reinterpret_cast<T*>(smem);
+    T* nxt = cur + total;
+    double* ls = reinterpret_cast<double*>(smem + ((2 * total * sizeof(T) + 7) & ~(size_t)7));
+    double* lf = ls + (y1 - y0) * EX;
+    const int units = (e1 - e0 + 2) / 3 * nx;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x);  // the wave's first unit
+    T c[kTriples][3][8], bd[kTriples][3];
+    int o[kTriples];
+    // b / diag of the thread's nodes; the mass weights (where nxt will be, with
+    // its zeros around), conductivities and fibre rows to LDS
+    {
+      const STM_GLOBAL T* __restrict__ di = gmem(dinv);
+      const STM_GLOBAL T* __restrict__ bg = gmem(b);
+      T d[kTriples][3], bb[kTriples][3];
+#pragma unroll
+      for (int n = 0; n < kTriples; ++n) {
+        const int q = min((int)threadIdx.x + n * BLOCK, units - 1);
+        const int t = fdiv(q, mnx), i = q - t * nx;
+        o[n] = pad + (e0 + 3 * t - s0) * nx + i;
+        if (wave + n * BLOCK < units) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r) {
+            const unsigned p = min(e0 + 3 * t + r, e1 - 1) * nx + i;
+            d[n][r] = di[p];
+            bb[n][r] = bg[p];
+          }
+        }
+      }
+      const STM_GLOBAL T* __restrict__ w = gmem(mgW(0)) + s0 * nx;
+      const STM_GLOBAL double* __restrict__ sg = gmem(sigma) + y0 * EX;
+      constexpr int U = 8;
+      const int nst = (s1 - s0) * nx, nse = (y1 - y0) * EX;
+      for (int qb = threadIdx.x; qb < max(nst, nse); qb += U * BLOCK) {
+        T rw[U];
+        double rs[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (qb + u * BLOCK < nst) rw[u] = w[(unsigned)(qb + u * BLOCK)];
+          if (qb + u * BLOCK < nse) rs[u] = sg[(unsigned)(qb + u * BLOCK)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (qb + u * BLOCK < nst) nxt[pad + qb + u * BLOCK] = rw[u];
+          if (qb + u * BLOCK < nse) ls[qb + u * BLOCK] = rs[u];
+        }
+      }
+      for (int q = threadIdx.x; q < kFibStride * (y1 - y0); q += BLOCK) lf[q] = cmem(Lp->fib[0])[kFibStride * y0 + q];
+      for (int q = threadIdx.x; q < total; q += BLOCK) cur[q] = T(0);
+      for (int q = threadIdx.x; q < total - nst; q += BLOCK) nxt[q < pad ? q : q + nst] = T(0);
+#pragma unroll
+      for (int n = 0; n < kTriples; ++n) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          const bool ok = (int)threadIdx.x + n * BLOCK < units && o[n] + r * nx < pad + (e1 - s0) * nx;
+          c[n][r][0] = ok ? d[n][r] : T(0);
+          bd[n][r] = ok ? d[n][r] * bb[n][r] : T(0);
+        }
+      }
+    }
+    __syncthreads();
+    // the coefficients, an element row after the other: of an element the
+    // stiffness couplings along x, along y and across both diagonals
+    {
+      const double tau = prm.tau, zr = prm.zr;
+      const T th = T(prm.theta), cxx = th * T(g.hy / (6.0 * g.hx)), cyy = th * T(g.hx / (6.0 * g.hy));
+      const T cxy = th * T(0.5), cm = T(g.hx * g.hy / 36.0);
+#pragma unroll
+      for (int n = 0; n < kTriples; ++n) {
+        if (wave + n * BLOCK < units) {
+          const int q = min((int)threadIdx.x + n * BLOCK, units - 1);
+          const int t = fdiv(q, mnx), i = q - t * nx, j0 = e0 + 3 * t;
+          const int el[2] = {max(i - 1, 0), min(i, EX - 1)};
+          struct Row {
+            T x[2], y[2], p[2], m[2], a[2];  // [element left, right of the node]
+          };
+          auto element_row = [&](int ey) {
+            Row R;
+            const bool in = ey >= 0 && ey < EY;
+            const int yy = min(max(ey, y0), y1 - 1) - y0;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const bool ok = in && (e ? i < nx - 1 : i > 0);
+              const Tensor2<T> D = tensor_from<T, 2>(ls[yy * EX + el[e]], lf + kFibStride * yy, tau, zr);
+              const T ax = ok ? cxx * D.xx : T(0), ay = ok ? cyy * D.yy : T(0), xy = ok ? cxy * D.xy : T(0);
+              R.x[e] = ay - T(2) * ax;
+              R.y[e] = ax - T(2) * ay;
+              R.p[e] = -(ax + ay) - xy;
+              R.m[e] = xy - (ax + ay);
+              R.a[e] = ok ? cm : T(0);
+            }
+            return R;
+          };
+          Row lo = element_row(j0 - 1);
+#pragma unroll
+          for (int r = 0; r < 3; ++r) {
+            const Row hi = element_row(j0 + r);
+            const T* __restrict__ w = nxt + o[n] + r * nx;
+            const T d = c[n][r][0];
+            c[n][r][0] = d * (lo.x[0] + hi.x[0] + T(2) * (lo.a[0] + hi.a[0]) * w[-1]);
+            c[n][r][1] = d * (lo.x[1] + hi.x[1] + T(2) * (lo.a[1] + hi.a[1]) * w[1]);
+            c[n][r][2] = d * (lo.y[0] + lo.y[1] + T(2) * (lo.a[0] + lo.a[1]) * w[-nx]);
+            c[n][r][3] = d * (hi.y[0] + hi.y[1] + T(2) * (hi.a[0] + hi.a[1]) * w[nx]);
+            c[n][r][4] = d * (lo.p[0] + lo.a[0] * w[-nx - 1]);
+            c[n][r][5] = d * (hi.p[1] + hi.a[1] * w[nx + 1]);
+            c[n][r][6] = d * (lo.m[1] + lo.a[1] * w[-nx + 1]);
+            c[n][r][7] = d * (hi.m[0] + hi.a[0] * w[nx - 1]);
+            lo = hi;
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int a = 0; a < 8; ++a) c[n][r][a] = T(0);
+        }
+      }
+    }
+    __syncthreads();  // the weights are read
+    T* xg[2] = {mgT(0), V + vstride};  // x of the rows that the neighbours read
+    int parity = 0, age = 0;
+#pragma unroll 1
+    for (int s = 1; s <= nc; ++s) {
+      if (age == H && G > 1) {
+        T* __restrict__ x = parity ? xg[1] : xg[0];
+        parity ^= 1;
+        age = 0;
+        const int hn = H * nx;
+        for (int q = threadIdx.x; q < 2 * hn; q += BLOCK) {
+          const bool up = q >= hn;
+          const int p = up ? (jb1 - H) * nx + q - hn : jb0 * nx + q;
+          if (up ? jb1 < ny : jb0 > 0) coh_store(gmem(x) + p, cur[pad + p - s0 * nx]);
+        }
+        halo_barrier();
+        for (int q = threadIdx.x; q < 2 * hn; q += BLOCK) {
+          const bool up = q >= hn;
+          const int p = up ? jb1 * nx + q - hn : (jb0 - H) * nx + q;
+          if (up ? jb1 < ny && p < s1 * nx : jb0 > 0 && p >= s0 * nx)
+            cur[pad + p - s0 * nx] = __hip_atomic_load(gmem(x) + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+      }
+      const T om = wgt(1, s - 1);
+#pragma unroll
+      for (int n = 0; n < kTriples; ++n) {
+        if (wave + n * BLOCK < units) {
+          int on = o[n];
+          asm volatile("" : "+v"(on));  // addresses formed here, not kept in registers across the sweeps
+          T v[5][3];
+#pragma unroll
+          for (int r = 0; r < 5; ++r)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) v[r][a] = cur[on + (r - 1) * nx + a - 1];
+          const bool mine = (int)threadIdx.x + n * BLOCK < units;
+          T xn[3];
+#pragma unroll
+          for (int r = 0; r < 3; ++r) {
+            const T y0 = c[n][r][0] * v[r + 1][0] + c[n][r][1] * v[r + 1][2];
+            const T y1 = c[n][r][2] * v[r][1] + c[n][r][3] * v[r + 2][1];
+            const T y2 = c[n][r][4] * v[r][0] + c[n][r][5] * v[r + 2][2];
+            const T y3 = c[n][r][6] * v[r][2] + c[n][r][7] * v[r + 2][0];
+            xn[r] = v[r + 1][1] + om * (bd[n][r] - v[r + 1][1] - ((y0 + y1) + (y2 + y3)));
+          }
+          const int end = pad + (e1 - s0) * nx;
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            if (mine && on + r * nx < end) nxt[on + r * nx] = xn[r];
+        }
+      }
+      ++age;
+      __syncthreads();
+      T* t = cur;
+      cur = nxt;
+      nxt = t;
+    }
+    // u += x, every thread's loads at once
+    constexpr int U = 8;
+    const int own = (jb1 - jb0) * nx;
+    const T* __restrict__ x = cur + pad + (jb0 - s0) * nx;
+    STM_GLOBAL double* __restrict__ ug = gmem(u) + jb0 * nx;
+    STM_GLOBAL T* __restrict__ og = gmem(out) + jb0 * nx;
+    double dm = 0.0;
+    for (int qb = threadIdx.x; qb < own; qb += U * BLOCK) {
+      double ru[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (qb + k * BLOCK < own) ru[k] = ug[(unsigned)(qb + k * BLOCK)];
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (qb + k * BLOCK < own) {
+          const T xn = x[qb + k * BLOCK];
+          og[(unsigned)(qb + k * BLOCK)] = xn;
+          ug[(unsigned)(qb + k * BLOCK)] = ru[k] + double(xn);
+          dm = fmax(dm, fabs(double(xn)));
+        }
+    }
+    return dm;
+  }
+
   // One defect correction of the slab's Newton equation (single-grid levels):
   // nc Chebyshev-weighted sweeps from x = 0 on A x = b with the weights of
   // omega row 1, the last sweep handing every owned node's value to fin.  3D
@@ -1568,10 +1821,6 @@ struct Team {
         if (!last) halo_barrier();
       }
     } else {
-      if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
-        jacobi_resident(b0, out0, nc, 1, fin);
-        return;
-      }
       const int P = (nc - 1) / 2;
 #pragma unroll 1
       for (int t = 1; t <= P; ++t)
@@ -1724,11 +1973,17 @@ struct Team {
     double dm = 0.0;
     double* __restrict__ u = io.u;
     bytes = uni(bytes + 16.0 * L->g[0].n);
-    chebyshev(V, Z, io.nc, io.x1 != 0, [&](NodeAt at, TI xn) {
-      const double dl = double(xn);
-      node_ref(u, at) += dl;
-      dm = fmax(dm, fabs(dl));
-    });
+    int H = 0;
+    if constexpr (DIM == 2) {
+      H = stencil_halo();
+      if (H > 0) dm = stencil_sweeps(V, Z, io.nc, H, u);
+    }
+    if (H == 0)
+      chebyshev(V, Z, io.nc, io.x1 != 0, [&](NodeAt at, TI xn) {
+        const double dl = double(xn);
+        node_ref(u, at) += dl;
+        dm = fmax(dm, fabs(dl));
+      });
     io.dmax = tmax(dm);  // its barrier also publishes u to the other members
   }
 

@@ -357,6 +357,7 @@ stm_status build_level(stm_ctx* c, int l, LevelHost& out) {
   // LDS tiles: maximise interior / staged nodes within the staging budget,
   // per field size and number of staged nodal fields (2 to 4)
   const size_t budget = (size_t)c->stage_bytes;
+  d.stage_bytes = c->stage_bytes;
   for (int k = 0; k < nmg && p.dim == 3; ++k) {
     // 3D passes march through the planes: a ring of three planes of two nodal
     // fields over the tile's rows plus a one-row halo (each field rounded up to
@@ -563,7 +564,7 @@ int team_cost(const stm_ctx* c, int level, int G) {
   const int block = auto_block(c->p, g.n, c->any_mg);
   int cost;
   const int rows = march_rows(g.nx, g.ex, d.tile_y[0][c->inner_fp32 ? 1 : 0][0], block);
-  return team_groups(c->p.dim, g.ny, g.nz, rows, G, &cost) ? cost : 0;
+  return team_groups(c->p.dim, g.nx, g.ny, g.nz, rows, G, &cost) ? cost : 0;
 }
 
 // Largest team of at most `limit` workgroups that divides the level's grid.

@@ -75,6 +75,7 @@ struct LevelDev {
   // node rows per tile of the fused two-sweep smoother pass (2D), for 8-byte
   // and 4-byte inner vectors
   int tile_p8, tile_p4;
+  int stage_bytes;  // dynamic LDS of a solver workgroup
 };
 
 // Physics and solver parameters (uniform across a launch).
@@ -118,8 +119,11 @@ __host__ __device__ inline int march_rows(int nx, int ex, int lds_rows, int bloc
 // in every group but the first + about two steps of prologue), with at least 3
 // rows and 4 planes (less one where the groups' steps are evened out) per
 // member.  Returns Gz, 0 where there is no such division, and in `cost` the
-// rows (2D) or z-steps (3D) of a pass.
-__host__ __device__ inline int team_groups(int dim, int ny, int nz, int tile_rows, int G, int* cost) {
+// z-steps of a pass (3D) or a member's nodes plus what the barriers and
+// exchanges of a team cost in nodes (2D; 33x33 nodes, 64 steps: 5.8 ms alone,
+// 6.3 with three members, 7.0 with eleven; 129x129 per step and sample 84 us with
+// four, 71 with eight).
+__host__ __device__ inline int team_groups(int dim, int nx, int ny, int nz, int tile_rows, int G, int* cost) {
   int Gz = 0;
   *cost = 0;
   for (int d = 1; d <= (dim == 3 ? G : 1); ++d) {
@@ -127,7 +131,8 @@ __host__ __device__ inline int team_groups(int dim, int ny, int nz, int tile_row
     const int Gy = G / d;
     if (Gy > 1 && ny < 3 * Gy) continue;
     const int rows = (ny + Gy - 1) / Gy, steps = (nz + d - 1 + d - 1) / d;
-    const int c = dim == 3 ? ((rows + tile_rows - 1) / tile_rows) * (steps + 2) : rows + (G > 1 ? 2 : 0);
+    const int c = dim == 3 ? ((rows + tile_rows - 1) / tile_rows) * (steps + 2)
+                           : rows * nx + (G > 1 ? 1500 + 50 * G : 0);
     if (Gz == 0 || c < *cost) {
       *cost = c;
       Gz = d;

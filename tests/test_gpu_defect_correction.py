@@ -30,6 +30,17 @@ CASES = [
     # 2D, spectrum's interval, 40 slabs and a lane of three samples: several trials
     dict(shape=(17, 13), m=40, S=3, precision="fp64", G=1, lanes=1),
     dict(shape=(33, 25), m=24, S=2, precision="mixed", G=3),
+    # stencil in registers: deep and shallow halos, the widest rows, uneven bands,
+    # rows that do not fill a column of three; grids that do not fit (teams and alone)
+    dict(shape=(17, 31), m=6, S=2, precision="fp64", G=4),
+    dict(shape=(129, 40), m=4, S=2, precision="fp64", G=5),
+    dict(shape=(257, 23), m=4, S=1, precision="mixed", G=2),
+    dict(shape=(65, 65), m=4, S=1, precision="fp64", G=1),
+    dict(shape=(5, 9), m=6, S=2, precision="fp64", G=3),
+    dict(shape=(3, 3), m=4, S=2, precision="mixed", G=1),
+    dict(shape=(257, 11), m=4, S=1, precision="fp64", G=1),
+    dict(shape=(129, 65), m=4, S=1, precision="mixed", G=1),
+    dict(shape=(33, 33), m=6, S=2, precision="fp64", G=3, lds_kb=16),
     # 3D, rows split over members, planes split over members
     dict(shape=(9, 9, 5), m=24, S=2, precision="fp64", G=1),
     dict(shape=(9, 9, 17), m=20, S=2, precision="mixed", G=3),
@@ -70,7 +81,7 @@ def test_defect_corrections_match_oracle(torch_dev, c):
         over["max_lanes"] = c["lanes"]
     if "tuning" in c:
         over["level_tuning"] = [c["tuning"]]
-    for k in ("smoother", "smooth_omega", "newton_max"):
+    for k in ("smoother", "smooth_omega", "newton_max", "lds_kb"):
         if k in c:
             over[k] = c[k]
     with Context(wl, **over) as ctx:
