@@ -55,6 +55,16 @@ def _level_key(wl, l):
     return {"grid": list(wl["levels"][l]), "steps": int(wl["steps"][l])}
 
 
+def _max_team(wl, l):
+    """Largest team to measure: a member needs three rows, or in 3D also fewer planes."""
+    return MAX_TEAM if wl.get("dim", 2) == 3 else max(1, min(MAX_TEAM, int(wl["levels"][l][1]) // 3))
+
+
+def _teams_of(ctx, G):
+    t = ctx.timings()
+    return t["solve_blocks"] == G * t["solve_teams"]
+
+
 def tune(wl, precision=None, samples=32, candidates=None, seed=4242, block=0, log=print):
     """Measure every candidate on every level; return the tuning record."""
     import torch
@@ -75,7 +85,7 @@ def tune(wl, precision=None, samples=32, candidates=None, seed=4242, block=0, lo
     for l in range(len(wl["levels"])):
         S = max(2, min(samples, int(counts[l]) if counts else samples))
         m = int(wl["steps"][l])
-        gmax = max(1, min(MAX_TEAM, int(wl["levels"][l][1]) // 3))
+        gmax = _max_team(wl, l)
         large = float(np.prod(wl["levels"][l])) * m > LARGE
         wl_t, G_t, scale = wl, 1, 1.0
         if large:
@@ -135,7 +145,8 @@ def tune(wl, precision=None, samples=32, candidates=None, seed=4242, block=0, lo
                 sig = ctx.kl_synthesize(l, modes[l], xi)
                 try:
                     _, st = ctx.st_solve(l, sig)
-                    team[G - 1] = sum(s["device_seconds"] for s in st) / len(st)
+                    if _teams_of(ctx, G):  # else the grid has no division into G
+                        team[G - 1] = sum(s["device_seconds"] for s in st) / len(st)
                 except Exception as e:
                     log("level %d team %d: %s" % (l, G, e))
                 ctx.close()
@@ -158,7 +169,7 @@ def measure_teams(wl, rec, level, samples=None, seed=4343, log=print):
     M = wl["n_modes"]
     e = rec["levels"][level]
     m = int(wl["steps"][level])
-    gmax = max(1, min(MAX_TEAM, int(wl["levels"][level][1]) // 3))
+    gmax = _max_team(wl, level)
     large = float(np.prod(wl["levels"][level])) * m > LARGE
     S = samples or (LARGE_SAMPLES if large else 32)
     xi = torch.randn(S, M, generator=torch.Generator().manual_seed(seed), dtype=torch.float64).to(dev)
@@ -172,6 +183,8 @@ def measure_teams(wl, rec, level, samples=None, seed=4343, log=print):
         with Context(wl, precision=precision, level_tuning=tune_l, team_size=G, max_lanes=S * G) as ctx:
             sig = ctx.kl_synthesize(level, modes, xi)
             _, st = ctx.st_solve(level, sig)
+            if not _teams_of(ctx, G):  # the grid has no division into G
+                continue
         team[G - 1] = sum(s["device_seconds"] for s in st) / len(st)
         log("level %d team %d: %.4f s per sample" % (level, G, team[G - 1]))
     e["team_seconds"] = team
