@@ -10,8 +10,9 @@
 // spectrum of D^-1 A_k: the residual is evaluated anyway before the next step,
 // so a Krylov space would only repeat its work (per slab and at equal accuracy
 // 3 x 15 sweeps in 2D and 3 x 26 in 3D take the place of 60-70 and 100-120
-// inside GMRES with its products, dots and updates: 33^2 x 64 steps 20.5 -> 8.9
-// ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms, 65x65x17 x 32 x 16 98 -> 59 ms).
+// inside GMRES with its products, dots and updates: with the passes of that
+// time 33^2 x 64 steps 20.5 -> 8.9 ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms,
+// 65x65x17 x 32 x 16 98 -> 59 ms; with those of now 4.9, 16.2 and 43).
 // Where it does not contract, and with a V-cycle, the linear step is GMRES,
 // right-preconditioned by one geometric-multigrid V-cycle with weighted-Jacobi
 // smoothing on the slab operator A_k = M/dt + K - M diag f'(u_k) (with one
