@@ -150,8 +150,10 @@ typedef struct {
   int lds_kb;                 /* LDS staging budget per workgroup in KiB: 144 */
   int block_threads;          /* threads per workgroup: chosen from the grid size */
   int max_lanes;              /* workgroups per solver launch: 1024 (capped by co-residency) */
-  int team_size;              /* workgroups per sample in stm_st_solve: 0 = chosen from S and the
-                                 device; >1 only with mg_levels = 1 */
+  int team_size;              /* workgroups per sample in stm_st_solve: 0 = chosen from S, the grid and
+                                 the device; else the largest size up to it that divides the grid
+                                 (3 rows per member; 3D: planes too, 4 per member); >1 only with
+                                 mg_levels = 1 */
   double theta;               /* weight of the new time level in the diffusion term, in [1/2, 1]:
                                  1 (default; 0 selects it) backward Euler, 1/2 the paper's
                                  Crank-Nicolson (Sec. 3.2, eq. st-system: A = M + dt/2 K,
