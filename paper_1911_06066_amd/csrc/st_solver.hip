@@ -80,6 +80,12 @@ __device__ __forceinline__ double uni(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// |v| for a maximum: fmax drops a NaN, so a value that is not finite counts as infinite.
+__device__ __forceinline__ double abs_or_inf(double v) {
+  const double a = fabs(v);
+  return a < HUGE_VAL ? a : HUGE_VAL;
+}
+
 // Global-memory views of generic pointers.  An access through a generic
 // pointer that the compiler cannot place compiles to a flat instruction, and
 // flat instructions count against the LDS wait counter as well: every LDS wait
@@ -1784,7 +1790,7 @@ struct Team {
           const T xn = x[qb + k * BLOCK];
           og[(unsigned)(qb + k * BLOCK)] = xn;
           ug[(unsigned)(qb + k * BLOCK)] = ru[k] + double(xn);
-          dm = fmax(dm, fabs(double(xn)));
+          dm = fmax(dm, abs_or_inf(double(xn)));
         }
     }
     return dm;
@@ -1983,7 +1989,7 @@ struct Team {
       chebyshev(V, Z, io.nc, io.x1 != 0, [&](NodeAt at, TI xn) {
         const double dl = double(xn);
         node_ref(u, at) += dl;
-        dm = fmax(dm, fabs(dl));
+        dm = fmax(dm, abs_or_inf(dl));
       });
     io.dmax = tmax(dm);  // its barrier also publishes u to the other members
   }
@@ -2256,7 +2262,7 @@ struct Team {
                 if (qb + v * BLOCK < nb) {
                   u[ix[v]] = uo[v] + dl[v];
                   dlt[ix[v]] = dl[v];
-                  dm = fmax(dm, fabs(dl[v]));
+                  dm = fmax(dm, abs_or_inf(dl[v]));
                 }
               }
             }
@@ -3120,7 +3126,7 @@ __global__ __launch_bounds__(BLOCK) void st_global_kernel(const LevelDev* __rest
           const int idx = tm.bidx(q);
           const double dl = double(gZ[k * vs + idx]);
           U[(int64_t)k * n0 + idx] += dl;
-          dm = fmax(dm, fabs(dl));
+          dm = fmax(dm, abs_or_inf(dl));
         }
       dmax = uni(tm.tmax(dm));  // its barrier also publishes U to the other members
       const double ach = sh_resid / beta;

@@ -1,0 +1,65 @@
+"""GPU: when a slab's defect corrections end, and what they leave behind.
+
+Corrections that overflow, stall at rounding or do not contract give way to
+GMRES; none of it may reach the accepted state or the following samples.
+"""
+
+import numpy as np
+import pytest
+
+import oracle.api as oapi
+import stinputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(shape, m, S, precision="fp64", **kw):
+    dim = len(shape)
+    base = "small_mc_2d" if dim == 2 else "slab3d"
+    wl = stinputs.workload(base, levels=[shape], steps=[m], n_modes=8, precision=precision,
+                           kl_grid=(17, 17) if dim == 2 else (9, 9, 3), ic_radius=0.3, sigma_f0=4e-3)
+    wl["T"] = m / 64.0
+    wl.update(kw)
+    basis = oapi.kl_basis(wl)
+    sig = oapi.kl_synthesize(oapi.kl_modes(wl, 0, basis), stinputs.xi(base, 0, S, wl["n_modes"]), wl["sigma_f0"])
+    return wl, sig
+
+
+def _initial(wl):
+    """The initial state: the ball of the workload, x fastest."""
+    shape = wl["levels"][0]
+    ax = [np.linspace(0.0, l, n) for n, l in zip(shape, wl["lengths"])]
+    g = np.meshgrid(*reversed(ax), indexing="ij")
+    d2 = sum((x - c) ** 2 for x, c in zip(reversed(g), wl["ic_center"]))
+    return (d2 <= wl["ic_radius"] ** 2).astype(np.float64).reshape(-1)
+
+
+@pytest.mark.parametrize("damping", [0, -1])
+@pytest.mark.parametrize("shape", [(17, 13), (9, 9, 5)])
+def test_correction_that_overflows_is_not_accepted(shape, damping):
+    """A guess of 1e14 puts the residual beyond float32: every node of the
+    float32 correction, or the nodes around one, is infinite or NaN.  GMRES takes
+    the slab from the previous state, as for corrections that are far too large."""
+    import torch
+    from paper_1911_06066_amd import Context
+    wl, sig = _setup(shape, 1, 3, "mixed")
+    n = int(np.prod(shape))
+    guess = np.tile(_initial(wl), (3, 1)).reshape(3, 1, n)
+    guess[0] += 1e14
+    guess[1, 0, n // 2] += 1e14
+    with Context(wl, team_size=1, newton_damping=damping) as ctx:
+        u, stats = ctx.st_solve(0, torch.from_numpy(sig).cuda(), u0_guess=torch.from_numpy(guess).cuda())
+    assert all(s["status"] == 0 for s in stats)
+    U_ref, _ = oapi.st_solve(wl, 0, sig, mode="timestep")
+    assert np.abs(u.cpu().numpy() - U_ref).max() < 1e-8  # float32 corrections; NaN fails
+
+
+def test_newton_step_that_overflows_is_reported():
+    """The same guess with fixed weights, which take GMRES: the step is not a number."""
+    import torch
+    from paper_1911_06066_amd import Context, StmError
+    wl, sig = _setup((17, 13), 1, 1, "mixed")
+    guess = _initial(wl).reshape(1, 1, -1) + 1e14
+    with Context(wl, smoother=1) as ctx, pytest.raises(StmError) as e:
+        ctx.st_solve(0, torch.from_numpy(sig).cuda(), u0_guess=torch.from_numpy(guess).cuda())
+    assert e.value.code == "STM_E_NONFINITE"
