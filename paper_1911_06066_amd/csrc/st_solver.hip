@@ -2530,6 +2530,9 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       // damping: the residual 2-norm of the last accepted iterate and the
       // fraction of the last Newton step in u (halved while the residual grows)
       double beta_acc = 0.0, tstep = 1.0;
+      // what u has had since then: a defect correction (in Z), a Newton step
+      // (in dlt), or neither
+      bool corrected = false, stepped = false;
       bool cheb = nc > 0;
       int ncor = 0;  // defect corrections of the slab (not counted against newton_max)
       int cost = 0;
@@ -2547,7 +2550,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         STM_T1(t_res, 0);
         model_bytes = uni(model_bytes + 32.0 * n0);
         const double beta = uni(sqrt(io.resid));
-        if (!isfinite(beta) && !(prm.damping && it > 0 && tstep > kMinStep)) {
+        if (!isfinite(beta) && !corrected && !(prm.damping && stepped && tstep > kMinStep)) {
           status = -5;
           break;
         }
@@ -2559,9 +2562,9 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         // a defect correction that did not contract the residual well (the
         // first one may owe its remainder to the reaction) leaves the rest of
         // the slab to GMRES; one that made it grow is taken back
-        if (cheb && ncor > 0 && !(beta <= (ncor == 1 ? 0.5 : kContract) * beta_acc)) {
+        if (corrected && !(beta <= (ncor == 1 ? 0.5 : kContract) * beta_acc)) {
           if constexpr (!MG) {
-            if (beta <= beta_acc && !wide && step + trial > 0) {  // first the whole interval
+            if (cheb && beta <= beta_acc && !wide && step + trial > 0) {  // first the whole interval
               wide = true;
               nc = tm.cheb_interval(low0, lmax0, 0);
               io.x1 = 0;
@@ -2577,16 +2580,17 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             }
             tm.bytes = uni(tm.bytes + (16.0 + sizeof(TI)) * n0);
             beta_acc = HUGE_VAL;
+            corrected = false;
             dprev = 0.0;
             ++ncor;
             tm.sync();
             continue;
           }
         }
-        // the last step made the residual grow (or not finite): take half of
+        // the last Newton step made the residual grow (or not finite): take half of
         // it back, u -= (t/2) delta, and evaluate again (Armijo-style halving
         // down to kMinStep; the pass counts as a Newton iteration)
-        if (prm.damping && it > 0 && !(beta <= beta_acc) && tstep > kMinStep) {
+        if (prm.damping && stepped && !(beta <= beta_acc) && tstep > kMinStep) {
           tstep = uni(0.5 * tstep);
           for (int q = tid; q < nb; q += BLOCK) {
             const int idx = tm.bidx(q);
@@ -2600,6 +2604,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         }
         beta_acc = beta;
         tstep = 1.0;
+        corrected = stepped = false;
         // ---- smoother weights: once per sample, from the first slab operator ----
         if (!weights_ready) {
           if constexpr (MG) {
@@ -2627,6 +2632,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             io.nc = nc;
             do_step<kStepCorrect>(tm, io, &calls, smem_dyn, red, omega_tab);
             dmax = uni(io.dmax);
+            corrected = true;
             STM_T1(t_ch, 1);
             ++krylov_total;
             ++ncor;
@@ -2637,7 +2643,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
                 u[idx] = uprev[idx];
               }
               nc = 0;
-              cheb = false;
+              cheb = corrected = false;
               beta_acc = HUGE_VAL;
               dprev = 0.0;
               tm.sync();
@@ -2675,6 +2681,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         krylov_total += io.jdim;
         model_bytes = uni(io.model_bytes);
         dmax = uni(io.dmax);
+        stepped = true;
         const double ach = io.resid / beta;
         if (!isfinite(dmax)) {
           status = -5;

@@ -63,3 +63,39 @@ def test_newton_step_that_overflows_is_reported():
     with Context(wl, smoother=1) as ctx, pytest.raises(StmError) as e:
         ctx.st_solve(0, torch.from_numpy(sig).cuda(), u0_guess=torch.from_numpy(guess).cuda())
     assert e.value.code == "STM_E_NONFINITE"
+
+
+def test_last_correction_of_a_slab_leaves_no_step_to_halve():
+    """Sixteen corrections that end at rounding are followed by GMRES.  The
+    residual may have grown a little by then, and what the Newton damping would
+    halve is GMRES's step, of which there has been none: the launch before filled
+    that vector with NaN.
+
+    k_react is tiny (a linear problem), the guesses are random by amounts spread
+    over the decades that sixteen corrections of degree 5 cover, and newton_tol is
+    out of reach, so that every sample ends at the Newton limit, near its solution.
+    """
+    import torch
+    from paper_1911_06066_amd import Context, StmError
+    S = 512
+    wl, sig = _setup((9, 9), 1, 8, "mixed", k_react=1e-9)
+    sig = np.repeat(sig, S // 8, axis=0)
+    u0 = _initial(wl)
+    rng = np.random.default_rng(5)
+    amp = 10.0 ** np.linspace(-1.0, 2.4, S)
+    guess = u0 + amp[:, None, None] * rng.uniform(-1.0, 1.0, (S, 1, 81))
+    bad = np.tile(u0, (S, 1, 1))
+    bad[:, 0, 40] += 1e30
+    for tuning in ((5, 8.5), (5, 9.5)):
+        with Context(wl, newton_tol=1e-40, newton_max=4, max_lanes=S, team_size=1, level_tuning=[tuning]) as ctx:
+            u = torch.empty((S, 1, 81), dtype=torch.float64, device="cuda")
+            # stiffness far above mass away from a node with a huge value: GMRES at once, on infinities
+            try:
+                ctx.st_solve(0, torch.from_numpy(1e4 * sig).cuda(), u0_guess=torch.from_numpy(bad).cuda(), out=u)
+            except StmError:
+                pass
+            with pytest.raises(StmError) as e:
+                ctx.st_solve(0, torch.from_numpy(sig).cuda(), u0_guess=torch.from_numpy(guess).cuda(), out=u)
+        assert e.value.code == "STM_E_NOT_CONVERGED"
+        U_ref, _ = oapi.st_solve(wl, 0, sig[:: S // 8], mode="timestep")
+        assert np.abs(u.cpu().numpy()[:: S // 8] - U_ref).max() < 1e-9
