@@ -156,15 +156,13 @@ constexpr int kPartStride = 16;       // doubles per member in the partials buff
 constexpr double kMinStep = 1.0 / 64;  // smallest damped fraction of a Newton step
 constexpr unsigned kSpinLimit = 1u << 25;
 // Defect corrections by Chebyshev sweeps.  A slab keeps to them while each
-// contracts the residual by kContract; after kMaxFallbacks slabs in a row that
-// did not, the sample gives them up for GMRES.
+// contracts the residual by kContract; after more than kMaxFallbacks slabs in a
+// row that did not, the sample gives them up for GMRES.
 constexpr double kContract = 0.1;
 constexpr int kMaxFallbacks = 2;
 constexpr int kMaxCorrections = 16;  // per slab
 constexpr double kChebTol = 0.003;   // of newton_tol: predicted size of the next correction
-constexpr double kChebReduction = 1e-4;  // error reduction of a correction over the whole interval
-constexpr double kChebNarrow = 1.4;  // interval ratio between one step of narrowing and the next
-constexpr int kCorrectionCost = 5;   // residual and update of a correction, in sweeps
+constexpr double kChebReduction = 1e-4;  // error reduction of a correction
 
 template <int DIM>
 __device__ __forceinline__ void decode(const GridDev& g, int idx, int& i, int& j, int& k) {
@@ -1864,20 +1862,18 @@ struct Team {
     return pm <= 1.0 && low > 0.0 ? low : 0.0;
   }
 
-  // Chebyshev weights of the defect corrections into omega row 1; returns the
-  // degree.  Narrowing step 0 covers [low, lmax] with an error reduction of
-  // 1e-4: 1e-3, 5e-4, 2e-4 and 1e-4 need 4, 3-3.5, 3 and 3 corrections per slab
-  // there.  Each further step divides the ratio lmax / low by kChebNarrow: where
-  // the solution is smooth the modes below the interval are hardly there, and
-  // fewer sweeps reduce the rest as far.  A level with its own sweep count or
-  // ratio keeps those.  Between two workgroup barriers.
-  __device__ __forceinline__ int cheb_interval(double low, double lmax, int step) const {
-    double ratio = lmax / low;
-    for (int i = 0; i < step; ++i) ratio /= kChebNarrow;
-    if (L->own_ratio > 0.0) ratio = L->own_ratio;
+  // Chebyshev weights of the defect corrections into omega row 1, for the
+  // spectrum's interval [low, lmax] and an error reduction of 1e-4 (1e-3, 5e-4,
+  // 2e-4 and 1e-4 need 4, 3-3.5, 3 and 3 corrections per slab); returns the
+  // degree.  A level with its own sweep count or ratio keeps those.  The interval
+  // is never narrower than the spectrum: corrections do not see the modes left
+  // out, and a slab would be accepted with their error.  Between two workgroup
+  // barriers.
+  __device__ __forceinline__ int cheb_interval(double low, double lmax) const {
+    const double ratio = L->own_ratio > 0.0 ? L->own_ratio : lmax / low;
     const double rt = sqrt(ratio), rho = (rt - 1.0) / (rt + 1.0);
     int nc = L->own_sweeps;
-    if (nc <= 0) nc = (int)ceil(log(2.0 / (step ? 2.0 * kChebReduction : kChebReduction)) / -log(rho));
+    if (nc <= 0) nc = (int)ceil(log(2.0 / kChebReduction) / -log(rho));
     nc = min(max(nc, 3), kMaxSweeps);
     if (nc % 2 != (DIM == 2 ? 1 : 0)) nc = nc < kMaxSweeps ? nc + 1 : nc - 1;  // 2D odd, 3D even
     nc = __builtin_amdgcn_readfirstlane(nc);
@@ -1885,12 +1881,6 @@ struct Team {
     if (threadIdx.x == 0) chebyshev_weights(lmax / ratio, lmax, nc, omega + kMaxSweeps);
     __syncthreads();
     return nc;
-  }
-  __device__ __forceinline__ int cheb_steps(double low, double lmax) const {  // narrowing steps down to a ratio of 3
-    if (L->own_ratio > 0.0 || L->own_sweeps > 0) return 0;
-    int g = 0;
-    for (double r = lmax / low / kChebNarrow; r > 3.0 && g < 8; r /= kChebNarrow) ++g;
-    return __builtin_amdgcn_readfirstlane(g);
   }
 
   // lmax of D^-1 A_l by power iteration.
@@ -2454,14 +2444,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
 
   bool have_prev = false;
   const double* prevU = nullptr;
-  // Interval of the defect corrections, narrowing step `step`: every `wait`
-  // slabs one slab tries a narrower one and keeps it when it took less.  Trials
-  // go `jump` steps, one and three in turn while they fail (with fewer sweeps
-  // a step may need one correction more and the third step none); after each
-  // such pair the time to the next one doubles.
-  int step = 0, jump = 1, wait = 3, backoff = 8;
-  int slab_cost = 0;
-
   for (int it_s = 0; it_s < task.count; ++it_s) {
     const int s = task.order ? task.order[task.first + it_s * task.stride] : task.first + it_s * task.stride;
     const long long t_start = wall_clock64();
@@ -2504,8 +2486,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
     // many slabs in a row have had to fall back on GMRES
     int nc = 0, fallbacks = 0;
     double lmax0 = 0.0, low0 = 0.0;
-    int ngrow = 0;   // narrowing steps there are
-    if (wait < 2) wait = 2;
 
     for (int k = 0; k < m; ++k) {
       // ---- initial iterate of slab k ----
@@ -2535,12 +2515,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       bool corrected = false, stepped = false;
       bool cheb = nc > 0;
       int ncor = 0;  // defect corrections of the slab (not counted against newton_max)
-      int cost = 0;
-      bool wide = false;  // the slab has gone back to the whole interval
-      const bool trial = cheb && step + jump <= ngrow && --wait <= 0;
-      if constexpr (!MG) {
-        if (trial) nc = tm.cheb_interval(low0, lmax0, step + jump);
-      }
       for (; it - ncor < prm.newton_max; ++it) {
         // ---- residual (float64) -> V_0, Jacobian weights on every grid ----
         // 3D defect corrections start with the sweep from zero, om r / diag, there
@@ -2563,16 +2537,8 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
         // first one may owe its remainder to the reaction) leaves the rest of
         // the slab to GMRES; one that made it grow is taken back
         if (corrected && !(beta <= (ncor == 1 ? 0.5 : kContract) * beta_acc)) {
-          if constexpr (!MG) {
-            if (cheb && beta <= beta_acc && !wide && step + trial > 0) {  // first the whole interval
-              wide = true;
-              nc = tm.cheb_interval(low0, lmax0, 0);
-              io.x1 = 0;
-            } else {
-              cheb = false;
-              if (++fallbacks > kMaxFallbacks) nc = 0;
-            }
-          }
+          cheb = false;
+          if (++fallbacks > kMaxFallbacks) nc = 0;
           if (!(beta <= beta_acc)) {
             for (int q = tid; q < nb; q += BLOCK) {
               const int idx = tm.bidx(q);
@@ -2614,9 +2580,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             lmax0 = uni(io.dmax);
             low0 = uni(io.resid);
             if (low0 > 0.0 && lmax0 > low0 && lmax0 < 100.0 * low0) {
-              ngrow = tm.cheb_steps(low0, lmax0);
-              step = min(step, ngrow);
-              nc = tm.cheb_interval(low0, lmax0, step);
+              nc = tm.cheb_interval(low0, lmax0);
               cheb = true;
             }
           }
@@ -2636,7 +2600,6 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             STM_T1(t_ch, 1);
             ++krylov_total;
             ++ncor;
-            cost += nc + kCorrectionCost;
             if (!(dmax < 1e3)) {  // far out of range or not finite: GMRES from the previous slab's state
               for (int q = tid; q < nb; q += BLOCK) {
                 const int idx = tm.bidx(q);
@@ -2706,36 +2669,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       }
       if (status == -5) break;
       if (!conv && status == 0) status = -4;
-      if constexpr (!MG) {
-        if (cheb) {
-          fallbacks = 0;
-          if (trial) {
-            const bool better = !wide && 32 * cost < 31 * slab_cost;
-            if (better) {
-              step += jump;
-              slab_cost = cost;
-              wait = 1;
-              backoff = 8;
-            } else {
-              nc = tm.cheb_interval(low0, lmax0, step);
-              wait = jump == 1 ? 2 : backoff;
-              if (jump > 1) backoff = min(2 * backoff, 64);
-              jump = jump == 1 ? 3 : 1;
-            }
-            if (step + jump > ngrow) jump = 1;
-          } else {
-            if (step > 0 && (wide || 8 * cost > 9 * slab_cost)) {  // the solution has changed: one step back
-              step -= 1;
-              wait = backoff;
-              nc = tm.cheb_interval(low0, lmax0, step);
-            }
-            slab_cost = cost;
-          }
-        } else if (nc > 0) {
-          step = 0;
-          nc = tm.cheb_interval(low0, lmax0, 0);
-        }
-      }
+      if (cheb) fallbacks = 0;
       newton_total += it;
       newton_max_slab = max(newton_max_slab, it);
       worst_final = uni(fmax(worst_final, dmax));
