@@ -1835,16 +1835,20 @@ struct Team {
   }
 
   // Lower end of the spectrum of D^-1 A for the Chebyshev interval, 0 when
-  // defect corrections are not for this operator.  From the diagonal's
-  // stiffness to mass ratio r at the nodes: on a uniform grid the Q1 mass matrix
-  // relative to its diagonal is smallest, 2^-d, on the mode that alternates
-  // along every axis, where the stiffness is 2^(2-d) of its diagonal whatever
-  // the anisotropy, so that D^-1 A there is 2^-d (1 + 4 r) / (1 + r) (r capped
-  // where another mode may be lower); the constant has (3/2)^d / (1 + r).  The
-  // smallest of both over the nodes, less 5%, lay 5-20% below the smallest
-  // eigenvalue on every workload's operators.
+  // defect corrections are not for this operator.  On a uniform grid the modes
+  // that alternate along some of the axes and are constant along the others
+  // bound it: relative to the diagonal the Q1 mass matrix is 1/2 on such a mode
+  // for each axis it alternates along and 3/2 for each other, and the stiffness
+  // along axis a is twice the other axes' factors where the mode alternates along
+  // a, else 0.  With r the diagonal's stiffness to mass ratio and f_a the axes'
+  // shares of the stiffness, D^-1 A there is (mass + r sum f_a stiffness_a) / (1 + r);
+  // the smallest over the modes and both ends of r at the nodes, with the smallest
+  // share of each axis over the elements, less 5%, is a lower bound for every
+  // operator tried (0.5-0.94 of the smallest eigenvalue; without the modes along
+  // single axes 2.3 times it on 7x7x41 nodes with a stiffness of 3 mass).
   __device__ __forceinline__ double spectrum_low() const {
-    const double th = prm.theta;
+    const GridDev& g = L->g[0];
+    const double th = prm.theta, tau = prm.tau, zr = prm.zr;
     const TI* __restrict__ di = dinv;
     double pm = 0.0, qm = 0.0;  // largest mass and stiffness share of the diagonal
     const int nb = nband();
@@ -1856,10 +1860,37 @@ struct Team {
     }
     qm = tmax(qm);
     pm = tmax(pm);
-    const double rc = fmin(fmax(0.0, 1.0 / pm - 1.0), 0.5);
-    const double d2 = (DIM == 3) ? 0.125 : 0.25, d3 = (DIM == 3) ? 3.375 : 2.25;
-    const double low = 0.95 * fmin(d2 * (1.0 + 4.0 * rc) / (1.0 + rc), d3 * (1.0 - qm));
-    return pm <= 1.0 && low > 0.0 ? low : 0.0;
+    double f[DIM];  // 1 less an axis's share, largest; then the smallest share
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) f[a] = 0.0;
+    const int layer = DIM == 3 ? g.ex * g.ey : g.ex;  // elements of a fibre-table row
+    for (int e = rank * BLOCK + threadIdx.x; e < g.ne; e += G * BLOCK) {
+      const auto D = tensor_from<double, DIM>(sigma[e], L->fib[0] + kFibStride * (e / layer), tau, zr);
+      double w[DIM], sum = 0.0;
+      w[0] = D.xx / (g.hx * g.hx);
+      w[1] = D.yy / (g.hy * g.hy);
+      if constexpr (DIM == 3) w[2] = D.zz / (g.hz * g.hz);
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) sum += w[a];
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) f[a] = fmax(f[a], 1.0 - w[a] / sum);
+    }
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) f[a] = 1.0 - tmax(f[a]);
+    const double r0 = fmax(0.0, 1.0 / pm - 1.0), r1 = 1.0 / fmax(1.0 - qm, 1e-300) - 1.0;
+    double low = HUGE_VAL;
+#pragma unroll
+    for (int k = 0; k < (1 << DIM); ++k) {  // bit a: alternating along axis a
+      double m = 1.0, st = 0.0;
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) m *= (k >> a & 1) ? 0.5 : 1.5;
+#pragma unroll
+      for (int a = 0; a < DIM; ++a)
+        if (k >> a & 1) st += f[a] * 2.0 * (m / 0.5);
+      low = fmin(low, fmin((m + r0 * st) / (1.0 + r0), (m + r1 * st) / (1.0 + r1)));
+    }
+    low *= 0.95;
+    return pm <= 1.0 && qm < 1.0 && low > 0.0 ? low : 0.0;
   }
 
   // Chebyshev weights of the defect corrections into omega row 1, for the

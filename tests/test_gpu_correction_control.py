@@ -139,3 +139,20 @@ def test_result_with_a_guess_does_not_depend_on_the_batch(shape, precision):
         for s in range(S):
             one, _ = ctx.st_solve(0, sig[s:s + 1].contiguous(), u0_guess=guess[s:s + 1].contiguous())
             assert torch.equal(one[0], u[s])
+
+
+@pytest.mark.parametrize("shape,kw", [((12, 200), {}), ((200, 12), {}), ((13, 40), dict(sigma_f0=0.03)),
+                                      ((7, 7, 41), dict(sigma_f0=0.02)), ((41, 7, 5), dict(sigma_f0=0.02))])
+def test_corrections_contract_on_anisotropic_grids(shape, kw):
+    """Where one axis carries nearly all of the stiffness, the smallest eigenvalues
+    belong to modes that alternate along another: the interval reaches them, so
+    that few corrections (at most six a slab) do."""
+    import torch
+    from paper_1911_06066_amd import Context
+    m = 16
+    wl, sig = _setup(shape, m, 1, T=m / 46.0, **kw)
+    with Context(wl) as ctx:
+        u, st = ctx.st_solve(0, torch.from_numpy(sig).cuda())
+    U_ref, _ = oapi.st_solve(wl, 0, sig, mode="timestep")
+    assert np.abs(u.cpu().numpy() - U_ref).max() < 1e-9
+    assert st[0]["krylov_iters"] == st[0]["newton_iters"] <= 6 * m
