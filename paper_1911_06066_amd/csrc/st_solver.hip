@@ -161,8 +161,18 @@ constexpr unsigned kSpinLimit = 1u << 25;
 constexpr double kContract = 0.1;
 constexpr int kMaxFallbacks = 2;
 constexpr int kMaxCorrections = 16;  // per slab
-constexpr double kChebTol = 0.003;   // of newton_tol: predicted size of the next correction
-constexpr double kChebReduction = 1e-4;  // error reduction of a correction
+// A correction's degree follows from the error reduction wanted of it, in bits
+// (log2): kFirstBits of a slab's first one, whose remainder Newton's own exceeds
+// soon (10 bits in 2D, where a correction costs as much as 25 sweeps, 6.5 in 3D,
+// where it costs 5: 32 samples of 129x129 nodes 9.7 ms, 10.9 with 7), at least
+// kLeastBits, well inside kContract, and with float32 sweeps at most kFloatBits.
+// A slab is accepted with an error of kLeft newton_tol.  Drawn solves are then 8e-14 off
+// in the median, 5e-13 at most, with newton_tol 1e-10; kLeft 1e-5 makes it 9e-16
+// and 2e-15 for 1.11 of the time.
+constexpr int kMaxDegree = 48;
+constexpr float kFirstBits2 = 10.0f, kFirstBits3 = 6.5f, kLeastBits = 5.0f, kFloatBits = 20.0f;
+constexpr double kLeft = 1e-3;
+constexpr double kRounding = 1e-15;  // u is O(1)
 
 template <int DIM>
 __device__ __forceinline__ void decode(const GridDev& g, int idx, int& i, int& j, int& k) {
@@ -228,11 +238,12 @@ __device__ __forceinline__ double react_d(double u, double kr, double ar) {
 }
 
 // Weights 1 / xi_s, xi_s the roots of the degree-K Chebyshev polynomial
-// shifted to [a, b], ordered to alternate large and small roots.
-__device__ inline void chebyshev_weights(double a, double b, int K, double* w) {
+// shifted to [a, b], ordered to alternate large and small roots: every `stride`-th
+// from s0 on.
+__device__ inline void chebyshev_weights(double a, double b, int K, double* w, int s0 = 0, int stride = 1) {
   const double th = 0.5 * (b + a), de = 0.5 * (b - a);
   const double PI = 3.14159265358979323846;
-  for (int s = 0; s < K; ++s) {
+  for (int s = s0; s < K; s += stride) {
     const int r = (s % 2 == 0) ? s / 2 : K - 1 - s / 2;
     const double xi = th + de * cos(PI * (2 * r + 1) / (2.0 * K));
     w[s] = 1.0 / xi;
@@ -1893,25 +1904,27 @@ struct Team {
     return pm <= 1.0 && qm < 1.0 && low > 0.0 ? low : 0.0;
   }
 
-  // Chebyshev weights of the defect corrections into omega row 1, for the
-  // spectrum's interval [low, lmax] and an error reduction of 1e-4 (1e-3, 5e-4,
-  // 2e-4 and 1e-4 need 4, 3-3.5, 3 and 3 corrections per slab); returns the
-  // degree.  A level with its own sweep count or ratio keeps those.  The interval
-  // is never narrower than the spectrum: corrections do not see the modes left
-  // out, and a slab would be accepted with their error.  Between two workgroup
-  // barriers.
-  __device__ __forceinline__ int cheb_interval(double low, double lmax) const {
-    const double ratio = L->own_ratio > 0.0 ? L->own_ratio : lmax / low;
-    const double rt = sqrt(ratio), rho = (rt - 1.0) / (rt + 1.0);
-    int nc = L->own_sweeps;
-    if (nc <= 0) nc = (int)ceil(log(2.0 / kChebReduction) / -log(rho));
-    nc = min(max(nc, 3), kMaxSweeps);
-    if (nc % 2 != (DIM == 2 ? 1 : 0)) nc = nc < kMaxSweeps ? nc + 1 : nc - 1;  // 2D odd, 3D even
-    nc = __builtin_amdgcn_readfirstlane(nc);
+  // The next degree that a correction can have: 2D odd (a first sweep and pairs),
+  // 3D even (the last sweep ends in the output vector).
+  __device__ __forceinline__ int odd_or_even(int n) const {
+    if (n % 2 != (DIM == 2 ? 1 : 0)) n = n < kMaxDegree ? n + 1 : n - 1;
+    return __builtin_amdgcn_readfirstlane(n);
+  }
+  // Degree of a defect correction that reduces the error by 2^-bits: 2 rho^n on
+  // the interval, decay = -log2 rho.
+  __device__ __forceinline__ int cheb_degree(float decay, float bits) const {
+    return odd_or_even(min(max((int)ceilf((bits + 1.0f) / decay), 3), kMaxDegree));
+  }
+  __device__ __forceinline__ float cheb_decay(double ratio) const {
+    const double rt = sqrt(ratio);
+    return (float)log2((rt + 1.0) / (rt - 1.0));
+  }
+  // Weights of a defect correction into the omega table from row 1 on.  Between
+  // two workgroup barriers.
+  __device__ __forceinline__ void cheb_weights(double low, double lmax, int n) const {
     __syncthreads();
-    if (threadIdx.x == 0) chebyshev_weights(lmax / ratio, lmax, nc, omega + kMaxSweeps);
+    chebyshev_weights(low, lmax, n, omega + kMaxSweeps, threadIdx.x, BLOCK);
     __syncthreads();
-    return nc;
   }
 
   // lmax of D^-1 A_l by power iteration.
@@ -2513,10 +2526,14 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
     double worst_final = 0.0;
     bool weights_ready = (prm.smoother == 0);
     // defect correction by Chebyshev sweeps (the default way to a Newton step
-    // on single-grid levels): its degree (0: not used on this sample) and how
-    // many slabs in a row have had to fall back on GMRES
-    int nc = 0, fallbacks = 0;
+    // on single-grid levels): whether this sample takes it, the degree whose
+    // weights are in the table, the level's own degree, how many slabs in a row
+    // have had to fall back on GMRES, the interval with its decay per sweep, and
+    // the curvature: log2 of a slab's second correction over the square of its first
+    bool defect = false;
+    int nc = 0, fixed = 0, fallbacks = 0;
     double lmax0 = 0.0, low0 = 0.0;
+    float decay = 0.0f, curv = -3.0f;
 
     for (int k = 0; k < m; ++k) {
       // ---- initial iterate of slab k ----
@@ -2544,8 +2561,16 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
       // what u has had since then: a defect correction (in Z), a Newton step
       // (in dlt), or neither
       bool corrected = false, stepped = false;
-      bool cheb = nc > 0;
+      bool cheb = defect;
       int ncor = 0;  // defect corrections of the slab (not counted against newton_max)
+      float ldp = 0.0f;  // log2 of the last correction, and its degree
+      int ncp = 0;
+      if constexpr (!MG) {
+        if (cheb && !fixed) {
+          const int n1 = tm.cheb_degree(decay, DIM == 2 ? kFirstBits2 : kFirstBits3);
+          if (n1 != nc) tm.cheb_weights(low0, lmax0, nc = n1);
+        }
+      }
       for (; it - ncor < prm.newton_max; ++it) {
         // ---- residual (float64) -> V_0, Jacobian weights on every grid ----
         // 3D defect corrections start with the sweep from zero, om r / diag, there
@@ -2565,11 +2590,11 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
           break;
         }
         // a defect correction that did not contract the residual well (the
-        // first one may owe its remainder to the reaction) leaves the rest of
+        // first two may owe their remainder to the reaction) leaves the rest of
         // the slab to GMRES; one that made it grow is taken back
-        if (corrected && !(beta <= (ncor == 1 ? 0.5 : kContract) * beta_acc)) {
+        if (corrected && !(beta <= (ncor <= 2 ? 0.5 : kContract) * beta_acc)) {
           cheb = false;
-          if (++fallbacks > kMaxFallbacks) nc = 0;
+          if (++fallbacks > kMaxFallbacks) defect = false;
           if (!(beta <= beta_acc)) {
             for (int q = tid; q < nb; q += BLOCK) {
               const int idx = tm.bidx(q);
@@ -2611,8 +2636,23 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             lmax0 = uni(io.dmax);
             low0 = uni(io.resid);
             if (low0 > 0.0 && lmax0 > low0 && lmax0 < 100.0 * low0) {
-              nc = tm.cheb_interval(low0, lmax0);
-              cheb = true;
+              // The interval is the spectrum's and never narrower by itself:
+              // corrections do not see the modes left out, and slabs would be
+              // accepted with their error.  A level's own sweeps and ratio are
+              // taken where they contract; where they do not they are GMRES's.
+              const double own = L->own_ratio > 0.0 ? L->own_ratio : lmax0 / low0;
+              const int n = L->own_sweeps > 0 ? tm.odd_or_even(max(L->own_sweeps, 3)) : 0;
+              decay = tm.cheb_decay(own);
+              fixed = 0;
+              if (n == 0 || exp2f(1.0f - L->own_sweeps * decay) <= (float)kContract) {
+                low0 = lmax0 / own;
+                fixed = n;
+              } else {
+                decay = tm.cheb_decay(lmax0 / low0);
+              }
+              nc = fixed ? fixed : tm.cheb_degree(decay, DIM == 2 ? kFirstBits2 : kFirstBits3);
+              tm.cheb_weights(low0, lmax0, nc);
+              defect = cheb = true;
             }
           }
           __syncthreads();
@@ -2636,29 +2676,36 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
                 const int idx = tm.bidx(q);
                 u[idx] = uprev[idx];
               }
-              nc = 0;
-              cheb = corrected = false;
+              defect = cheb = corrected = false;
               beta_acc = HUGE_VAL;
               dprev = 0.0;
               tm.sync();
               continue;
             }
-            if (dmax <= prm.newton_tol) {
+            // The error left, as log2: what the degree leaves of it, or what is
+            // seen of the contraction so far (corrections contract linearly, at
+            // a rate per sweep), or Newton's own remainder, whichever is most.
+            const float ld = log2f(fmaxf((float)dmax, 1e-37f));
+            float shrink = 1.0f - nc * decay;
+            if (sizeof(TI) == 4) shrink = fmaxf(shrink, -kFloatBits);
+            if (ncor == 2) curv = ld - 2.0f * ldp;
+            if (ncor >= 2) shrink = fmaxf(shrink, fminf((ld - ldp) * nc / ncp, 0.0f));
+            const float left = fmaxf(ld + shrink, curv + 2.0f * ld);
+            const float goal = log2f((float)fmax(kLeft * prm.newton_tol, kRounding));
+            if (left <= goal && left <= log2f((float)prm.newton_tol)) {
               conv = true;
               ++it;
               break;
             }
-            // Corrections contract linearly: the next one, which is also the
-            // error left, is about dmax times the last contraction.  The bound
-            // is stricter than for the Newton steps below, which mostly end far
-            // below their estimate.
-            if (it >= 1) {
-              const double ratio = dmax / dprev;
-              if (ratio < 0.5 && dmax * fmax(ratio, kChebReduction) <= kChebTol * prm.newton_tol) {
-                conv = true;
-                ++it;
-                break;
-              }
+            // the next correction's degree: down to the goal or to Newton's
+            // remainder, in equal parts where that is more than one can give
+            ncp = nc;
+            ldp = ld;
+            if (!fixed && ncor < kMaxCorrections) {
+              const float bits = fmaxf(left - fmaxf(goal - 1.0f, curv + 2.0f * left), kLeastBits);
+              const float most = sizeof(TI) == 4 ? fminf(kMaxDegree * decay - 1.0f, kFloatBits) : kMaxDegree * decay - 1.0f;
+              const int n = tm.cheb_degree(decay, bits / ceilf(bits / most));
+              if (n != nc) tm.cheb_weights(low0, lmax0, nc = n);
             }
             dprev = uni(dmax);
             eta = uni(fmax(prm.gmres_rtol, fmin(1e-4, 0.01 * dmax)));

@@ -141,6 +141,30 @@ def test_result_with_a_guess_does_not_depend_on_the_batch(shape, precision):
             assert torch.equal(one[0], u[s])
 
 
+@pytest.mark.parametrize("c", [
+    dict(shape=(17, 13), m=24, theta=1.0), dict(shape=(33, 33), m=32, theta=0.5), dict(shape=(33, 25), m=24, S=2, G=3),
+    dict(shape=(17, 17), m=24, ic_kind="gauss", ic_radius=0.5), dict(shape=(17, 17), m=16, sigma_f0=0.1),
+    dict(shape=(9, 9, 5), m=24), dict(shape=(9, 9, 9), m=16, theta=0.5, ic_kind="gauss", ic_radius=0.5),
+    dict(shape=(17, 17), m=8, tuning=(13, 9.0)), dict(shape=(9, 9, 5), m=8, tuning=(20, 20.0)),
+    # settings that do not contract by themselves are for GMRES only
+    dict(shape=(17, 17), m=16, tuning=(3, 30.0)), dict(shape=(9, 9, 5), m=16, tuning=(4, 10.0)),
+])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_corrections_leave_a_thousandth_of_the_newton_tolerance(c, precision):
+    """A slab's corrections end with a remainder of 1e-3 newton_tol = 1e-13 by the
+    contraction seen, which m slabs can add up to m 1e-13."""
+    import torch
+    from paper_1911_06066_amd import Context
+    kw = {k: c[k] for k in ("theta", "ic_kind", "ic_radius", "sigma_f0") if k in c}
+    wl, sig = _setup(c["shape"], c["m"], c.get("S", 1), precision, **kw)
+    over = dict(level_tuning=[c["tuning"]]) if "tuning" in c else {}
+    with Context(wl, team_size=c.get("G", 1), **over) as ctx:
+        u, stats = ctx.st_solve(0, torch.from_numpy(sig).cuda())
+    assert all(s["krylov_iters"] == s["newton_iters"] for s in stats)  # corrections only
+    U_ref, _ = oapi.st_solve(wl, 0, sig, mode="timestep")
+    assert np.abs(u.cpu().numpy() - U_ref).max() < c["m"] * 1e-13
+
+
 @pytest.mark.parametrize("shape,kw", [((12, 200), {}), ((200, 12), {}), ((13, 40), dict(sigma_f0=0.03)),
                                       ((7, 7, 41), dict(sigma_f0=0.02)), ((41, 7, 5), dict(sigma_f0=0.02))])
 def test_corrections_contract_on_anisotropic_grids(shape, kw):
