@@ -1553,31 +1553,14 @@ struct Team {
   }
 
   // ---- corrections with the stencil in registers (2D) -----------------------
-  // Columns of three nodes per thread: 55 registers each in float64, 28 in
-  // float32, so that nothing spills inside the sweeps at 512 threads.
-  static constexpr int kTriples = sizeof(TI) == 8 ? 3 : 4;
+  static constexpr int kTriples = stencil_triples(sizeof(TI));
   // Halo depth of stencil_sweeps, 0 where the member's rows do not fit its
-  // registers or the LDS (jacobi_pair then).  A correction of about 12 sweeps
-  // takes 8.1 us per column a thread holds (3.3 to set up, 0.4 per sweep) and
-  // 1.6 us per exchange, of which there are 12 / h.
+  // registers or the LDS (jacobi_pair then).
   __device__ __forceinline__ int stencil_halo() const {
     const STM_CONST LevelDev* __restrict__ Lp = cmem(here(L));
     const STM_CONST GridDev& g = Lp->g[0];
-    const int rows = (g.ny + G - 1) / G;
-    int best = 0, low = 0;
-    for (int h = 1; h <= (G == 1 ? 1 : min(g.ny / G, 6)); ++h) {
-      const int ext = min(rows + 2 * (h - 1), g.ny);
-      const int cols = ((ext + 2) / 3 * g.nx + BLOCK - 1) / BLOCK;
-      const int words = 2 * ((min(rows + 2 * h, g.ny) + 5) * g.nx + 2) + 1;
-      const int lds = words * (int)sizeof(TI) + (min(ext + 1, g.ey)) * (g.ex + kFibStride) * 8 + 8;
-      if (cols > kTriples || lds > Lp->stage_bytes) break;
-      const int c = 81 * cols + 190 / h;
-      if (!best || c < low) {
-        low = c;
-        best = h;
-      }
-    }
-    return __builtin_amdgcn_readfirstlane(best);
+    return __builtin_amdgcn_readfirstlane(
+        stencil_halo_depth(g.nx, g.ny, g.ex, g.ey, G, BLOCK, (int)sizeof(TI), Lp->stage_bytes));
   }
   // The sweeps of a defect correction with the scaled operator D^-1 A of every
   // node in registers: x += om (D^-1 b - D^-1 A x) takes eight products per node

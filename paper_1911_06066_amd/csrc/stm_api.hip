@@ -574,22 +574,36 @@ int max_team(const stm_ctx* c, int level, int limit = kMaxTeam) {
   return std::max(1, G);
 }
 
+// Whether the rows of a member of a team of G fit the 2D sweeps with the stencil in
+// registers.
+bool team_fits(const stm_ctx* c, int level, int G) {
+  const GridDev& g = c->levels[level].dev.g[0];
+  return stencil_halo_depth(g.nx, g.ny, g.ex, g.ey, G, auto_block(c->p, g.n, c->any_mg), c->inner_fp32 ? 4 : 8,
+                            c->stage_bytes) > 0;
+}
+
 // The team of at most `limit` workgroups with the cheapest pass, the largest of
 // several: a 3D grid's passes depend on how the members divide into planes and
 // rows and not on their number alone.  16 samples of 41^3 nodes (float64, 24
 // steps): 60.8 ms with teams of 13, which divide into rows only, 23.8 with 12
 // and 21.4 with 16.  Of equal passes the larger team's have fewer rows: 8 samples
 // of 129x129x33 (float32 corrections, 16 steps) 60.8 ms with 24, 56.6 with 32.
+// In 2D the cost is that of sweeps in registers: of the teams whose rows fit, if
+// any does, else the largest team.  33x33 nodes with 16 KiB of LDS, where one
+// workgroup's rows do not fit: 4 samples x 16 steps take
+// 20.7 ms alone, 2.0 with the cheapest fitting team, 8.4 with the largest by GMRES.
 int best_team(const stm_ctx* c, int level, int limit) {
-  int best = 1, low = team_cost(c, level, 1);
-  for (int G = 2; G <= max_team(c, level, limit); ++G) {
+  const int most = max_team(c, level, limit);
+  int best = 0, low = 0;
+  for (int G = 1; G <= most; ++G) {
+    if (c->p.dim == 2 && !team_fits(c, level, G)) continue;
     const int cost = team_cost(c, level, G);
-    if (cost > 0 && cost <= low) {
+    if (cost > 0 && (best == 0 || cost <= low)) {
       low = cost;
       best = G;
     }
   }
-  return best;
+  return best > 0 ? best : most;
 }
 
 // Workgroups that can be resident at once for the solver configuration.

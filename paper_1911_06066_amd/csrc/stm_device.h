@@ -149,6 +149,36 @@ __host__ __device__ inline int team_groups(int dim, int nx, int ny, int nz, int 
 // (1 - ratio) cos sin), tau = 0 and zr = ratio, which with ratio 1 is sigma_e I.
 constexpr int kFibStride = 3;
 
+// Columns of three nodes per thread in the sweeps with the stencil in registers
+// (2D): 55 registers each in float64, 28 in float32.
+__host__ __device__ constexpr int stencil_triples(int word) { return word == 8 ? 3 : 4; }
+
+// Halo depth of these sweeps on a member of a team of G, 0 where its rows do not
+// fit the registers or the LDS.  A correction of about 12 sweeps takes 8.1 us per
+// column a thread holds (3.3 to set up, 0.4 per sweep) and 1.6 us per exchange, of
+// which there are 12 / h.
+__host__ __device__ inline int stencil_halo_depth(int nx, int ny, int ex, int ey, int G, int block, int word,
+                                                  int stage_bytes) {
+  const int rows = (ny + G - 1) / G;
+  const int deepest = G == 1 ? 1 : (ny / G < 6 ? ny / G : 6);
+  int best = 0, low = 0;
+  for (int h = 1; h <= deepest; ++h) {
+    const int ext = rows + 2 * (h - 1) < ny ? rows + 2 * (h - 1) : ny;      // computed rows
+    const int staged = rows + 2 * h < ny ? rows + 2 * h : ny;
+    const int erows = ext + 1 < ey ? ext + 1 : ey;
+    const int cols = ((ext + 2) / 3 * nx + block - 1) / block;
+    const int words = 2 * ((staged + 5) * nx + 2) + 1;
+    const int lds = words * word + erows * (ex + kFibStride) * 8 + 8;
+    if (cols > stencil_triples(word) || lds > stage_bytes) break;
+    const int c = 81 * cols + 190 / h;
+    if (!best || c < low) {
+      low = c;
+      best = h;
+    }
+  }
+  return best;
+}
+
 // A team of G workgroups solves `count` samples s = first + i * stride in
 // order.  One TeamTask per workgroup: the members of a team carry identical
 // fields except `rank`.  With G > 1 each member owns a band of node rows of
