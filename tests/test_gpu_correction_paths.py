@@ -55,3 +55,46 @@ def test_team_of_a_2d_solve_fits_the_register_sweeps(c):
     s = stats[0]
     assert s["krylov_iters"] == s["newton_iters"]
     assert s["algorithmic_bytes"] == _register_bytes(c["shape"], 4, p, s["newton_iters"])
+
+
+@pytest.mark.parametrize("c", [
+    # 2D with the stencil in registers: bands of teams, deep and shallow halos, one
+    # workgroup at the ends of what fits 256 and 512 threads
+    dict(shape=(17, 31), G=4, register=True), dict(shape=(129, 40), G=5, register=True),
+    dict(shape=(257, 23), precision="mixed", G=2, register=True), dict(shape=(5, 9), G=3, register=True),
+    dict(shape=(3, 3), precision="mixed", G=1, register=True), dict(shape=(33, 33), G=1, register=True),
+    dict(shape=(65, 65), G=1, register=True), dict(shape=(45, 45), G=1, register=True),
+    dict(shape=(257, 11), G=1, register=True),
+    # more columns of three nodes than the threads hold: 833 of 3 x 256, 1806 of 3 x 512, 2838 of 4 x 512
+    dict(shape=(49, 49), G=1, register=False), dict(shape=(129, 40), G=1, register=False),
+    dict(shape=(129, 65), precision="mixed", G=1, register=False),
+    # 3D: bands of rows, groups of planes
+    dict(shape=(9, 9, 5), G=1), dict(shape=(9, 9, 17), precision="mixed", G=3), dict(shape=(13, 13, 13), G=12),
+])
+def test_corrections_run_on_the_team_and_sweeps_meant(c):
+    p = c.get("precision", "fp64")
+    stats, G = _solve(c["shape"], 4, 1, p, team_size=c["G"])
+    assert G == c["G"]
+    s = stats[0]
+    assert s["krylov_iters"] == s["newton_iters"]  # no GMRES
+    if "register" in c:
+        b = _register_bytes(c["shape"], 4, p, s["newton_iters"])
+        assert (s["algorithmic_bytes"] == b) if c["register"] else (s["algorithmic_bytes"] > 1.2 * b)
+
+
+@pytest.mark.parametrize("c", [
+    dict(shape=(17, 17), smoother=1), dict(shape=(9, 9, 9), precision="mixed", smoother=1, smooth_omega=0.4),
+    dict(shape=(17, 17), mg_levels=2), dict(shape=(17, 17, 9), mg_levels=-1),
+])
+def test_fixed_weights_and_v_cycles_take_gmres(c):
+    over = {k: v for k, v in c.items() if k not in ("shape", "precision")}
+    stats, _ = _solve(c["shape"], 4, 1, c.get("precision", "fp64"), **over)
+    assert stats[0]["krylov_iters"] > 1.5 * stats[0]["newton_iters"]
+
+
+def test_settings_for_gmres_do_not_make_failed_corrections():
+    """A level's own settings that do not contract leave the corrections as they are without."""
+    free, _ = _solve((17, 17), 8, 1, "fp64", team_size=1)
+    for tuning in ((2, 5.0), (4, 10.0), (8, 30.0)):
+        s, _ = _solve((17, 17), 8, 1, "fp64", team_size=1, level_tuning=[tuning])
+        assert (s[0]["newton_iters"], s[0]["krylov_iters"]) == (free[0]["newton_iters"], free[0]["krylov_iters"])
