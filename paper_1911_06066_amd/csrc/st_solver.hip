@@ -1265,12 +1265,9 @@ struct Team {
   // grid fits one tile (2D): the mass weights, b, dinv, sigma and the fibre
   // rows are staged once; the first sweep (from x = 0) is om b dinv, the later
   // ones alternate between two LDS vectors, and the last is written to out.
-  // Each sweep takes the operations of a single sweep in the same order; row
-  // is the weights' row of the omega table, fin as in jacobi_pair (every call
-  // is a last pass).  Ends with a workgroup barrier.
-  template <typename Fin>
-  __device__ __forceinline__ void jacobi_resident(const TI* __restrict__ b, TI* __restrict__ out, int nc, int row,
-                                                  Fin fin) const {
+  // Each sweep takes the operations of a single sweep in the same order.  Ends
+  // with a workgroup barrier.
+  __device__ __forceinline__ void jacobi_resident(const TI* __restrict__ b, TI* __restrict__ out, int nc) const {
     static_assert(DIM == 2, "the resident smoother is 2D");
     using T = TI;
     constexpr int NV = 4;
@@ -1335,12 +1332,10 @@ struct Team {
     __syncthreads();
     // ---- sweep 1 from x = 0 ----
     {
-      const T om = wgt(row, 0);
+      const T om = wgt(0, 0);
       T* dst = nc == 1 ? out : lx0;
       for (int q = threadIdx.x; q < nst; q += BLOCK) {
-        const T xn = om * lb[q] * ld[q];
-        dst[q] = xn;
-        if (nc == 1) fin(NodeAt{0, (unsigned)q}, xn);
+        dst[q] = om * lb[q] * ld[q];
       }
       __syncthreads();
     }
@@ -1381,7 +1376,7 @@ struct Team {
       }
       __syncthreads();
       // ---- phase B: every node ----
-      const T om = wgt(row, s - 1);
+      const T om = wgt(0, s - 1);
       for (int q = threadIdx.x; q < nst; q += BLOCK) {
         const int j = fdiv(q, mnx);
         const int i = q - j * nx;
@@ -1403,7 +1398,6 @@ struct Team {
         const T xn = cur[q] + om * (lb[q] - y) * ld[q];
         if (s == nc) {
           out[q] = xn;
-          fin(NodeAt{0, (unsigned)q}, xn);
         } else {
           nxt[q] = xn;
         }
@@ -1492,7 +1486,6 @@ struct Team {
       TI* buf[2] = {mgT(0), out0};
       const int nc = L->sweeps;
       if constexpr (DIM == 3) {
-        // sweep s (1-based) of nc writes buf[(nc - s + 1) % 2]: the last one out0
         jacobi(0, b0, nullptr, buf[nc % 2], wgt(0, 0));
         for (int s = 2; s <= nc; ++s) jacobi(0, b0, buf[(nc - s + 2) % 2], buf[(nc - s + 1) % 2], wgt(0, s - 1));
       } else {
@@ -1501,7 +1494,7 @@ struct Team {
         // pass each), and a single sweep when one is left.  Pass t (1-based) of
         // P writes buf[(P - t + 1) % 2]: the last one out0.
         if (G == 1 && (sizeof(TI) == 8 ? L->tile_p8 : L->tile_p4) >= L->g[0].ny) {
-          jacobi_resident(b0, out0, nc, 0, [](NodeAt, TI) {});
+          jacobi_resident(b0, out0, nc);
           return;
         }
         // With three or more sweeps the first pass runs sweeps 1 to 3 (the sweep
@@ -2028,262 +2021,262 @@ struct Team {
     double model_bytes = io.model_bytes;
     const int tid = threadIdx.x, n0 = L->g[0].n, nb = nband(), restart = prm.restart;
     const int64_t vs = vstride;
-            // ---- GMRES(restart), right-preconditioned by the V-cycle ----
-            if (tid == 0) {
-              sc[0] = 1.0 / beta;
-              gv[0] = beta;
+    // ---- GMRES(restart), right-preconditioned by the V-cycle ----
+    if (tid == 0) {
+      sc[0] = 1.0 / beta;
+      gv[0] = beta;
+    }
+    __syncthreads();
+    const double tol_abs = uni(eta * beta);
+    int jdim = 0;
+    for (int j = 0; j < restart; ++j) {
+      TI* Vj = V + j * vs;
+      TI* Zj = Z + j * vs;
+      TI* Vn = V + (j + 1) * vs;
+      model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * (krylov_words + 2.0 * j));
+      STM_T0(t_vc);
+      vcycle(Vj, Zj);
+      STM_T1(t_vc, 1);
+      STM_T0(t_pa);
+      // pass A: ws = A Z_j (into V_{j+1})
+      bytes = uni(bytes + (3.0 * sizeof(TI) * n0 + dbytes(0)));
+      staged<TI, 0>(
+          0, Zj, mgW(0), (const TI*)nullptr, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
+          [](TI a, TI ww) { return ww * a; },
+          [&](int idx, int, int, int, TI w, TI, TI, TI, TI) { gmem(Vn)[idx] = w; });
+      STM_T1(t_pa, 2);
+      // Classical Gram-Schmidt against V_0..V_j, done twice when the inner
+      // vectors are float32 (CGS2: the second pass restores the orthogonality
+      // the first loses to rounding); each pass adds its projections to
+      // column j of H.
+      double nn[1] = {0.0};
+      constexpr int kPasses = sizeof(TI) == 4 ? 2 : 1;
+      // dots of the next pass, accumulated by the first pass's update
+      double dnext[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      bool have_dots = false;
+#pragma unroll 1
+      for (int pass = 0; pass < kPasses; ++pass) {
+        STM_T0(t_dot);
+        // dots with V_0..V_min(j,7) over the owned nodes: batched loads
+        double d[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) d[q] = have_dots ? dnext[q] : 0.0;
+        const int nk0 = min(j + 1, 8);
+        if (!have_dots) {
+          bytes = uni(bytes + ((1.0 + nk0) * sizeof(TI) * n0));
+          const TI* __restrict__ Vb = V;
+          const TI* __restrict__ Vr = Vn;
+          for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+            TI wv[2], vv[2][8];
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+              const int q = qb + uu * BLOCK;
+              const int idx = q < nb ? bidx(q) : 0;
+              wv[uu] = q < nb ? Vr[idx] : TI(0);
+#pragma unroll
+              for (int p = 0; p < 8; ++p) vv[uu][p] = (p < nk0 && q < nb) ? Vb[p * vs + idx] : TI(0);
             }
-            __syncthreads();
-            const double tol_abs = uni(eta * beta);
-            int jdim = 0;
-            for (int j = 0; j < restart; ++j) {
-              TI* Vj = V + j * vs;
-              TI* Zj = Z + j * vs;
-              TI* Vn = V + (j + 1) * vs;
-              model_bytes = uni(model_bytes + double(sizeof(TI)) * n0 * (krylov_words + 2.0 * j));
-              STM_T0(t_vc);
-              vcycle(Vj, Zj);
-              STM_T1(t_vc, 1);
-              STM_T0(t_pa);
-              // pass A: ws = A Z_j (into V_{j+1})
-              bytes = uni(bytes + (3.0 * sizeof(TI) * n0 + dbytes(0)));
-              staged<TI, 0>(
-                  0, Zj, mgW(0), (const TI*)nullptr, (const TI*)nullptr, KScale<TI>{TI(prm.theta)},
-                  [](TI a, TI ww) { return ww * a; },
-                  [&](int idx, int, int, int, TI w, TI, TI, TI, TI) { gmem(Vn)[idx] = w; });
-              STM_T1(t_pa, 2);
-              // Classical Gram-Schmidt against V_0..V_j, done twice when the inner
-              // vectors are float32 (CGS2: the second pass restores the orthogonality
-              // the first loses to rounding); each pass adds its projections to
-              // column j of H.
-              double nn[1] = {0.0};
-              constexpr int kPasses = sizeof(TI) == 4 ? 2 : 1;
-              // dots of the next pass, accumulated by the first pass's update
-              double dnext[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-              bool have_dots = false;
-    #pragma unroll 1
-              for (int pass = 0; pass < kPasses; ++pass) {
-                STM_T0(t_dot);
-                // dots with V_0..V_min(j,7) over the owned nodes: batched loads
-                double d[9];
-    #pragma unroll
-                for (int q = 0; q < 9; ++q) d[q] = have_dots ? dnext[q] : 0.0;
-                const int nk0 = min(j + 1, 8);
-                if (!have_dots) {
-                  bytes = uni(bytes + ((1.0 + nk0) * sizeof(TI) * n0));
-                  const TI* __restrict__ Vb = V;
-                  const TI* __restrict__ Vr = Vn;
-                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                    TI wv[2], vv[2][8];
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) {
-                      const int q = qb + uu * BLOCK;
-                      const int idx = q < nb ? bidx(q) : 0;
-                      wv[uu] = q < nb ? Vr[idx] : TI(0);
-    #pragma unroll
-                      for (int p = 0; p < 8; ++p) vv[uu][p] = (p < nk0 && q < nb) ? Vb[p * vs + idx] : TI(0);
-                    }
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu)
-    #pragma unroll
-                      for (int p = 0; p < 8; ++p) d[p] += double(vv[uu][p]) * double(wv[uu]);
-                  }
-                }
-                tsum<9>(d);
-                if (tid == 0) {
-    #pragma unroll
-                  for (int q = 0; q < 8; ++q)
-                    if (q < nk0) coef[q] = d[q];
-                }
-                for (int k0 = 8; k0 <= j; k0 += 8) {  // remaining dot chunks
-                  const int nk = min(j + 1 - k0, 8);
-                  bytes = uni(bytes + ((1.0 + nk) * sizeof(TI) * n0));
-    #pragma unroll
-                  for (int q = 0; q < 9; ++q) d[q] = 0.0;
-                  for (int q = tid; q < nb; q += BLOCK) {
-                    const int idx = bidx(q);
-                    const double wd = double(Vn[idx]);
-    #pragma unroll
-                    for (int p = 0; p < 8; ++p)
-                      if (p < nk) d[p] += double(V[(k0 + p) * vs + idx]) * wd;
-                  }
-                  tsum<9>(d);
-                  if (tid == 0) {
-    #pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                      if (q < nk) coef[k0 + q] = d[q];
-                  }
-                }
-                // projections onto the normalised basis enter H; V_q is stored with
-                // norm 1/sc[q], so w loses (sc[q]^2 <V_q, w>) V_q
-                if (tid == 0)
-                  for (int q = 0; q <= j; ++q) {
-                    const double hq = sc[q] * sc[j] * coef[q];
-                    H[q * kMaxRestart + j] = (pass ? H[q * kMaxRestart + j] : 0.0) + hq;
-                    coef[q] = sc[q] * sc[q] * coef[q];
-                  }
-                __syncthreads();
-                STM_T1(t_dot, 3);
-                STM_T0(t_pb);
-                // pass B: V_{j+1} -= sum_q coef_q V_q over the owned nodes; norm
-                nn[0] = 0.0;
-                bytes = uni(bytes + ((j + 3.0) * sizeof(TI) * n0));
-                // The first of two passes with at most 8 basis vectors also forms
-                // the second pass's dots from the values it holds: the same nodes
-                // per thread, the same operations in the same order as the
-                // separate loops, one read of the vectors fewer.
-                const bool fuse = pass + 1 < kPasses && j < 8;
-                if (fuse) {
-    #pragma unroll
-                  for (int q = 0; q < 9; ++q) dnext[q] = 0.0;
-                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                    double w[2];
-                    int ix[2];
-                    TI vv[2][8];
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) {
-                      const int q = qb + uu * BLOCK;
-                      ix[uu] = q < nb ? bidx(q) : 0;
-                      w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
-    #pragma unroll
-                      for (int p = 0; p < 8; ++p) vv[uu][p] = (p <= j && q < nb) ? V[p * vs + ix[uu]] : TI(0);
-                    }
-    #pragma unroll
-                    for (int p = 0; p < 8; ++p) {
-                      const double cq = p <= j ? coef[p] : 0.0;
-    #pragma unroll
-                      for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[uu][p]);
-                    }
-                    TI wt[2];
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) {
-                      wt[uu] = TI(0);
-                      if (qb + uu * BLOCK < nb) {
-                        wt[uu] = TI(w[uu]);
-                        Vn[ix[uu]] = wt[uu];
-                      }
-                    }
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu)
-    #pragma unroll
-                      for (int p = 0; p < 8; ++p) dnext[p] += double(vv[uu][p]) * double(wt[uu]);
-                  }
-                } else {
-                  // vectors in chunks of 4, all loads of a chunk issued before use
-                  for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-                    double w[2];
-                    int ix[2];
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) {
-                      const int q = qb + uu * BLOCK;
-                      ix[uu] = q < nb ? bidx(q) : 0;
-                      w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
-                    }
-                    for (int q0 = 0; q0 <= j; q0 += 4) {
-                      TI vv[4][2];
-    #pragma unroll
-                      for (int p = 0; p < 4; ++p)
-    #pragma unroll
-                        for (int uu = 0; uu < 2; ++uu)
-                          vv[p][uu] = (q0 + p <= j) ? V[(q0 + p) * vs + ix[uu]] : TI(0);
-    #pragma unroll
-                      for (int p = 0; p < 4; ++p) {
-                        const double cq = (q0 + p <= j) ? coef[q0 + p] : 0.0;
-    #pragma unroll
-                        for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[p][uu]);
-                      }
-                    }
-    #pragma unroll
-                    for (int uu = 0; uu < 2; ++uu) {
-                      if (qb + uu * BLOCK < nb) {
-                        const TI wt = TI(w[uu]);
-                        Vn[ix[uu]] = wt;
-                        nn[0] += double(wt) * double(wt);
-                      }
-                    }
-                  }
-                }
-                // Only the last pass's norm is used.  A member reads V_{j+1} at
-                // its own nodes only, and in the same thread-to-node order as it
-                // wrote them, so the first pass ends with a workgroup barrier.
-                have_dots = fuse;
-                if (pass + 1 < kPasses)
-                  __syncthreads();
-                else
-                  tsum<1>(nn);
-                STM_T1(t_pb, 4);
-              }
-              const double hn = uni(sqrt(nn[0]));
-              if (tid == 0) {
-                const double hj1 = sc[j] * hn;
-                sc[j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
-                for (int q = 0; q < j; ++q) {  // previous rotations on column j
-                  const double a = H[q * kMaxRestart + j], b = H[(q + 1) * kMaxRestart + j];
-                  H[q * kMaxRestart + j] = cs_[q] * a + sn_[q] * b;
-                  H[(q + 1) * kMaxRestart + j] = -sn_[q] * a + cs_[q] * b;
-                }
-                const double a = H[j * kMaxRestart + j];
-                const double r = sqrt(a * a + hj1 * hj1);
-                const double c = r > 0.0 ? a / r : 1.0, sn = r > 0.0 ? hj1 / r : 0.0;
-                cs_[j] = c;
-                sn_[j] = sn;
-                H[j * kMaxRestart + j] = r;
-                H[(j + 1) * kMaxRestart + j] = 0.0;
-                gv[j + 1] = -sn * gv[j];
-                gv[j] = c * gv[j];
-                sh_resid = fabs(gv[j + 1]);
-              }
-              __syncthreads();
-              jdim = j + 1;
-              const double resid = uni(sh_resid);
-              if (!(resid > tol_abs) || !(hn > 0.0)) break;
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu)
+#pragma unroll
+              for (int p = 0; p < 8; ++p) d[p] += double(vv[uu][p]) * double(wv[uu]);
+          }
+        }
+        tsum<9>(d);
+        if (tid == 0) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if (q < nk0) coef[q] = d[q];
+        }
+        for (int k0 = 8; k0 <= j; k0 += 8) {  // remaining dot chunks
+          const int nk = min(j + 1 - k0, 8);
+          bytes = uni(bytes + ((1.0 + nk) * sizeof(TI) * n0));
+#pragma unroll
+          for (int q = 0; q < 9; ++q) d[q] = 0.0;
+          for (int q = tid; q < nb; q += BLOCK) {
+            const int idx = bidx(q);
+            const double wd = double(Vn[idx]);
+#pragma unroll
+            for (int p = 0; p < 8; ++p)
+              if (p < nk) d[p] += double(V[(k0 + p) * vs + idx]) * wd;
+          }
+          tsum<9>(d);
+          if (tid == 0) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              if (q < nk) coef[k0 + q] = d[q];
+          }
+        }
+        // projections onto the normalised basis enter H; V_q is stored with
+        // norm 1/sc[q], so w loses (sc[q]^2 <V_q, w>) V_q
+        if (tid == 0)
+          for (int q = 0; q <= j; ++q) {
+            const double hq = sc[q] * sc[j] * coef[q];
+            H[q * kMaxRestart + j] = (pass ? H[q * kMaxRestart + j] : 0.0) + hq;
+            coef[q] = sc[q] * sc[q] * coef[q];
+          }
+        __syncthreads();
+        STM_T1(t_dot, 3);
+        STM_T0(t_pb);
+        // pass B: V_{j+1} -= sum_q coef_q V_q over the owned nodes; norm
+        nn[0] = 0.0;
+        bytes = uni(bytes + ((j + 3.0) * sizeof(TI) * n0));
+        // The first of two passes with at most 8 basis vectors also forms
+        // the second pass's dots from the values it holds: the same nodes
+        // per thread, the same operations in the same order as the
+        // separate loops, one read of the vectors fewer.
+        const bool fuse = pass + 1 < kPasses && j < 8;
+        if (fuse) {
+#pragma unroll
+          for (int q = 0; q < 9; ++q) dnext[q] = 0.0;
+          for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+            double w[2];
+            int ix[2];
+            TI vv[2][8];
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+              const int q = qb + uu * BLOCK;
+              ix[uu] = q < nb ? bidx(q) : 0;
+              w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
+#pragma unroll
+              for (int p = 0; p < 8; ++p) vv[uu][p] = (p <= j && q < nb) ? V[p * vs + ix[uu]] : TI(0);
             }
-            io.jdim = jdim;
-            if (tid == 0) {
-              for (int q = jdim - 1; q >= 0; --q) {
-                double acc = gv[q];
-                for (int p = q + 1; p < jdim; ++p) acc -= H[q * kMaxRestart + p] * yv[p];
-                yv[q] = acc / H[q * kMaxRestart + q];
-              }
-              for (int q = 0; q < jdim; ++q) coef[q] = yv[q] * sc[q];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+              const double cq = p <= j ? coef[p] : 0.0;
+#pragma unroll
+              for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[uu][p]);
             }
-            __syncthreads();
-            // ---- u += sum_q y_q z_q (float64) over the owned nodes, max-norm of the step ----
-            STM_T0(t_up);
-            double dm = 0.0;
-            bytes = uni(bytes + (double(jdim) * sizeof(TI) * n0 + 24.0 * n0));
-            for (int qb = tid; qb < nb; qb += BLOCK * 2) {
-              double dl[2] = {0.0, 0.0}, uo[2];
-              int ix[2];
-    #pragma unroll
-              for (int v = 0; v < 2; ++v) {
-                const int q = qb + v * BLOCK;
-                ix[v] = q < nb ? bidx(q) : 0;
-                uo[v] = q < nb ? u[ix[v]] : 0.0;
-              }
-              for (int q0 = 0; q0 < jdim; q0 += 4) {
-                TI zz[4][2];
-    #pragma unroll
-                for (int p = 0; p < 4; ++p)
-    #pragma unroll
-                  for (int v = 0; v < 2; ++v) zz[p][v] = (q0 + p < jdim) ? Z[(q0 + p) * vs + ix[v]] : TI(0);
-    #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                  const double cq = (q0 + p < jdim) ? coef[q0 + p] : 0.0;
-    #pragma unroll
-                  for (int v = 0; v < 2; ++v) dl[v] += cq * double(zz[p][v]);
-                }
-              }
-    #pragma unroll
-              for (int v = 0; v < 2; ++v) {
-                if (qb + v * BLOCK < nb) {
-                  u[ix[v]] = uo[v] + dl[v];
-                  dlt[ix[v]] = dl[v];
-                  dm = fmax(dm, abs_or_inf(dl[v]));
-                }
+            TI wt[2];
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+              wt[uu] = TI(0);
+              if (qb + uu * BLOCK < nb) {
+                wt[uu] = TI(w[uu]);
+                Vn[ix[uu]] = wt[uu];
               }
             }
-            io.dmax = uni(tmax(dm));  // its barrier also publishes u to the other members
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu)
+#pragma unroll
+              for (int p = 0; p < 8; ++p) dnext[p] += double(vv[uu][p]) * double(wt[uu]);
+          }
+        } else {
+          // vectors in chunks of 4, all loads of a chunk issued before use
+          for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+            double w[2];
+            int ix[2];
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+              const int q = qb + uu * BLOCK;
+              ix[uu] = q < nb ? bidx(q) : 0;
+              w[uu] = q < nb ? double(Vn[ix[uu]]) : 0.0;
+            }
+            for (int q0 = 0; q0 <= j; q0 += 4) {
+              TI vv[4][2];
+#pragma unroll
+              for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int uu = 0; uu < 2; ++uu)
+                  vv[p][uu] = (q0 + p <= j) ? V[(q0 + p) * vs + ix[uu]] : TI(0);
+#pragma unroll
+              for (int p = 0; p < 4; ++p) {
+                const double cq = (q0 + p <= j) ? coef[q0 + p] : 0.0;
+#pragma unroll
+                for (int uu = 0; uu < 2; ++uu) w[uu] -= cq * double(vv[p][uu]);
+              }
+            }
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+              if (qb + uu * BLOCK < nb) {
+                const TI wt = TI(w[uu]);
+                Vn[ix[uu]] = wt;
+                nn[0] += double(wt) * double(wt);
+              }
+            }
+          }
+        }
+        // Only the last pass's norm is used.  A member reads V_{j+1} at
+        // its own nodes only, and in the same thread-to-node order as it
+        // wrote them, so the first pass ends with a workgroup barrier.
+        have_dots = fuse;
+        if (pass + 1 < kPasses)
+          __syncthreads();
+        else
+          tsum<1>(nn);
+        STM_T1(t_pb, 4);
+      }
+      const double hn = uni(sqrt(nn[0]));
+      if (tid == 0) {
+        const double hj1 = sc[j] * hn;
+        sc[j + 1] = hn > 0.0 ? 1.0 / hn : 0.0;
+        for (int q = 0; q < j; ++q) {  // previous rotations on column j
+          const double a = H[q * kMaxRestart + j], b = H[(q + 1) * kMaxRestart + j];
+          H[q * kMaxRestart + j] = cs_[q] * a + sn_[q] * b;
+          H[(q + 1) * kMaxRestart + j] = -sn_[q] * a + cs_[q] * b;
+        }
+        const double a = H[j * kMaxRestart + j];
+        const double r = sqrt(a * a + hj1 * hj1);
+        const double c = r > 0.0 ? a / r : 1.0, sn = r > 0.0 ? hj1 / r : 0.0;
+        cs_[j] = c;
+        sn_[j] = sn;
+        H[j * kMaxRestart + j] = r;
+        H[(j + 1) * kMaxRestart + j] = 0.0;
+        gv[j + 1] = -sn * gv[j];
+        gv[j] = c * gv[j];
+        sh_resid = fabs(gv[j + 1]);
+      }
+      __syncthreads();
+      jdim = j + 1;
+      const double resid = uni(sh_resid);
+      if (!(resid > tol_abs) || !(hn > 0.0)) break;
+    }
+    io.jdim = jdim;
+    if (tid == 0) {
+      for (int q = jdim - 1; q >= 0; --q) {
+        double acc = gv[q];
+        for (int p = q + 1; p < jdim; ++p) acc -= H[q * kMaxRestart + p] * yv[p];
+        yv[q] = acc / H[q * kMaxRestart + q];
+      }
+      for (int q = 0; q < jdim; ++q) coef[q] = yv[q] * sc[q];
+    }
+    __syncthreads();
+    // ---- u += sum_q y_q z_q (float64) over the owned nodes, max-norm of the step ----
+    STM_T0(t_up);
+    double dm = 0.0;
+    bytes = uni(bytes + (double(jdim) * sizeof(TI) * n0 + 24.0 * n0));
+    for (int qb = tid; qb < nb; qb += BLOCK * 2) {
+      double dl[2] = {0.0, 0.0}, uo[2];
+      int ix[2];
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const int q = qb + v * BLOCK;
+        ix[v] = q < nb ? bidx(q) : 0;
+        uo[v] = q < nb ? u[ix[v]] : 0.0;
+      }
+      for (int q0 = 0; q0 < jdim; q0 += 4) {
+        TI zz[4][2];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+          for (int v = 0; v < 2; ++v) zz[p][v] = (q0 + p < jdim) ? Z[(q0 + p) * vs + ix[v]] : TI(0);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const double cq = (q0 + p < jdim) ? coef[q0 + p] : 0.0;
+#pragma unroll
+          for (int v = 0; v < 2; ++v) dl[v] += cq * double(zz[p][v]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        if (qb + v * BLOCK < nb) {
+          u[ix[v]] = uo[v] + dl[v];
+          dlt[ix[v]] = dl[v];
+          dm = fmax(dm, abs_or_inf(dl[v]));
+        }
+      }
+    }
+    io.dmax = uni(tmax(dm));  // its barrier also publishes u to the other members
     STM_T1(t_up, 5);
     io.model_bytes = model_bytes;
     io.resid = sh_resid;
