@@ -1830,9 +1830,9 @@ struct Team {
   // a, else 0.  With r the diagonal's stiffness to mass ratio and f_a the axes'
   // shares of the stiffness, D^-1 A there is (mass + r sum f_a stiffness_a) / (1 + r);
   // the smallest over the modes and both ends of r at the nodes, with the smallest
-  // share of each axis over the elements, less 5%, is a lower bound for every
-  // operator tried (0.5-0.94 of the smallest eigenvalue; without the modes along
-  // single axes 2.3 times it on 7x7x41 nodes with a stiffness of 3 mass).
+  // share of each axis over the elements, is a lower bound for every operator
+  // tried (0.54-0.99 of the smallest eigenvalue; without the modes along single
+  // axes 2.4 times it on 7x7x41 nodes with a stiffness of 3 mass).
   __device__ __forceinline__ double spectrum_low() const {
     const GridDev& g = L->g[0];
     const double th = prm.theta, tau = prm.tau, zr = prm.zr;
@@ -1876,7 +1876,6 @@ struct Team {
         if (k >> a & 1) st += f[a] * 2.0 * (m / 0.5);
       low = fmin(low, fmin((m + r0 * st) / (1.0 + r0), (m + r1 * st) / (1.0 + r1)));
     }
-    low *= 0.95;
     return pm <= 1.0 && qm < 1.0 && low > 0.0 ? low : 0.0;
   }
 
