@@ -82,9 +82,11 @@ typedef enum {
 /* One MLMC level: nodes per axis (nz = 1 in 2D; nx >= 3, ny >= 2 in 2D (a strip of one element
  * row with y-constant data is the 1D problem), ny >= 3 and nz >= 2 in 3D) and time steps.
  * smooth_sweeps and cheb_ratio override the problem's coarse_sweeps and
- * cheb_ratio for this level (0 keeps the problem's value) and fix the degree
- * and interval of its defect corrections (see mg_levels), which are otherwise
- * taken from the slab operator's spectrum and adapted from slab to slab. */
+ * cheb_ratio for this level (0 keeps the problem's value).  They also fix the
+ * degree and interval of its defect corrections (see mg_levels) if they reduce
+ * the error tenfold on that interval; otherwise these are taken from the slab
+ * operator's spectrum and the reduction wanted of each correction.  An interval
+ * narrower than the spectrum leaves error that the stopping rule does not see. */
 typedef struct {
   int nx, ny, nz;
   int m;
@@ -123,7 +125,10 @@ typedef struct {
   int precision;              /* stm_precision */
   /* solver controls; 0 selects the default */
   double newton_tol;          /* max-norm Newton step per slab (u is O(1)): 1e-10; a slab stops when its
-                                 step or the step predicted from the observed contraction is below it */
+                                 step or the step predicted from the observed contraction is below it,
+                                 defect corrections (see mg_levels) when the error they leave, by their
+                                 degree and the contraction observed, is below a thousandth of it (or
+                                 1e-15 if that is more) */
   int newton_max;             /* Newton iterations per slab (defect corrections, at most 16, not counted): 30 */
   double gmres_rtol;          /* relative Krylov residual: 1e-10 (fp64), 1e-5 (mixed) */
   int gmres_restart;          /* Krylov dimension of one linear solve: 16, at most 30; an unfinished

@@ -17,8 +17,9 @@ namespace stm {
 
 // Bound by HBM reads: a thread reads its node's time levels kActBatch at a time,
 // all loads of a batch in flight before the first comparison (one at a time, the
-// scan waited a memory round trip per level: 65x65x17 nodes x 256 levels x 8
-// samples 343 us, now 197 us; batches of 4 and 16 the same).
+// scan waited a memory round trip per level).  65x65x17 nodes x 256 levels x 8
+// samples: the call 345 -> 238 us, of which the kernel 199 (levels after a node's
+// crossing are not read); batches of 4 and 16 the same.
 constexpr int kActBatch = 8;
 
 __global__ __launch_bounds__(256) void activation_kernel(GridDev g, int m, double dt, double T, double thr,
