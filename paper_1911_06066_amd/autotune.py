@@ -1,13 +1,13 @@
 """Per-level smoother and team-size tuner with a JSON cache.
 
 The slab operators M/dt + K - M diag f'(u) of a level have a spectrum set by
-h and dt, so the best Jacobi sweep count K and Chebyshev interval ratio differ
-between levels: more sweeps make each defect correction dearer but fewer of
-them are needed.  The
-tuner solves a batch of samples of each level with every candidate (one
-workgroup per sample, as in the MLMC launch), keeps the candidate with the
-smallest mean workgroup-seconds per sample among those whose samples all
-converge.  With that smoother it then measures the seconds per sample for
+h and dt.  Defect corrections take their interval from it and their degree from
+the reduction wanted; on some levels a fixed sweep count K and interval ratio
+are faster.  The tuner solves a batch of samples of each level with every
+candidate (one workgroup per sample, as in the MLMC launch), keeps the candidate
+with the smallest mean workgroup-seconds per sample among those whose samples
+all converge and whose solutions agree with the automatic setting's.  Then
+it measures the seconds per sample with that smoother for
 teams of G workgroups (a sample's space-time solve split over G workgroups):
 the MLMC scheduler's starting cost model, refined by every later launch.
 Choices and measurements go to a JSON file.  The conductivity fields come

@@ -8,11 +8,11 @@
 // below tolerance, given the converged slab k-1.  On one grid a step is a defect
 // correction, delta = P(A_k) (-R_k) with P the Chebyshev iteration on the
 // spectrum of D^-1 A_k: the residual is evaluated anyway before the next step,
-// so a Krylov space would only repeat its work (per slab and at equal accuracy
-// 3 x 15 sweeps in 2D and 3 x 26 in 3D take the place of 60-70 and 100-120
-// inside GMRES with its products, dots and updates: with the passes of that
-// time 33^2 x 64 steps 20.5 -> 8.9 ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms,
-// 65x65x17 x 32 x 16 98 -> 59 ms; with those of now 4.9, 16.2 and 43).
+// so a Krylov space would only repeat its work (per slab about 45 sweeps in 2D and
+// 80 in 3D, in three corrections, take the place of 60-70 and 100-120 inside GMRES
+// with its products, dots and updates: with the passes of that time 33^2 x 64 steps
+// 20.5 -> 8.9 ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms, 65x65x17 x 32 x 16
+// 98 -> 59 ms; with those of now 5.2, 14.2 and 48).
 // Where it does not contract, and with a V-cycle, the linear step is GMRES,
 // right-preconditioned by one geometric-multigrid V-cycle with weighted-Jacobi
 // smoothing on the slab operator A_k = M/dt + K - M diag f'(u_k) (with one
@@ -1568,7 +1568,8 @@ struct Team {
   // conductivities and mass weights staged in LDS; what is left is bound by
   // latency (loads past a cold L2 after a team barrier, barriers, exchanges).
   // Per correction, before and after: 33x33 nodes on one workgroup 40 -> 16 us;
-  // 129x129 on teams of 8 95 -> 40; 257x257 in float32 on teams of 16 125 -> 42.  u += x; returns the member's max of |x|.
+  // 129x129 on teams of 8 95 -> 40; 257x257 in float32 on teams of 16 125 -> 42 (13
+  // to 15 sweeps each).  u += x; returns the member's max of |x|.
   __device__ __forceinline__ double stencil_sweeps(const TI* __restrict__ b, TI* __restrict__ out, int nc, int H,
                                                    double* __restrict__ u) const {
     static_assert(DIM == 2, "the sweeps in registers are 2D");
@@ -2678,7 +2679,7 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             ldp = ld;
             if (!fixed && ncor < kMaxCorrections) {
               const float bits = fmaxf(left - fmaxf(goal - 1.0f, curv + 2.0f * left), kLeastBits);
-              const float most = sizeof(TI) == 4 ? fminf(kMaxDegree * decay - 1.0f, kFloatBits) : kMaxDegree * decay - 1.0f;
+              const float most = fminf(kMaxDegree * decay - 1.0f, sizeof(TI) == 4 ? kFloatBits : 100.0f);
               const int n = tm.cheb_degree(decay, bits / ceilf(bits / most));
               if (n != nc) tm.cheb_weights(low0, lmax0, nc = n);
             }
