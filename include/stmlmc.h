@@ -82,11 +82,10 @@ typedef enum {
 /* One MLMC level: nodes per axis (nz = 1 in 2D; nx >= 3, ny >= 2 in 2D (a strip of one element
  * row with y-constant data is the 1D problem), ny >= 3 and nz >= 2 in 3D) and time steps.
  * smooth_sweeps and cheb_ratio override the problem's coarse_sweeps and
- * cheb_ratio for this level (0 keeps the problem's value).  They also fix the
- * degree and interval of its defect corrections (see mg_levels) if they reduce
- * the error tenfold on that interval; otherwise these are taken from the slab
- * operator's spectrum and the reduction wanted of each correction.  An interval
- * narrower than the spectrum leaves error that the stopping rule does not see. */
+ * cheb_ratio for this level (0 keeps the problem's value).  Sweeps above 0 also
+ * fix the degree and interval of its defect corrections (see mg_levels) if they
+ * reduce the error tenfold on the whole spectrum; otherwise these are taken from
+ * the slab operator's spectrum and the reduction wanted of each correction. */
 typedef struct {
   int nx, ny, nz;
   int m;

@@ -12,7 +12,7 @@
 // 80 in 3D, in three corrections, take the place of 60-70 and 100-120 inside GMRES
 // with its products, dots and updates: with the passes of that time 33^2 x 64 steps
 // 20.5 -> 8.9 ms, 129^2 x 64 x 32 samples 52.4 -> 25.5 ms, 65x65x17 x 32 x 16
-// 98 -> 59 ms; with those of now 5.2, 14.2 and 48).
+// 98 -> 59 ms; with those of now 5.2, 14.2 and 37).
 // Where it does not contract, and with a V-cycle, the linear step is GMRES,
 // right-preconditioned by one geometric-multigrid V-cycle with weighted-Jacobi
 // smoothing on the slab operator A_k = M/dt + K - M diag f'(u_k) (with one
@@ -169,6 +169,8 @@ constexpr int kMaxCorrections = 16;  // per slab
 // A slab is accepted with an error of kLeft newton_tol.  Drawn solves are then 8e-14 off
 // in the median, 5e-13 at most, with newton_tol 1e-10; kLeft 1e-5 makes it 9e-16
 // and 2e-15 for 1.11 of the time.
+// Corrections are for spectra up to kWidest.
+constexpr double kWidest = 100.0;
 constexpr int kMaxDegree = 48;
 constexpr float kFirstBits2 = 10.0f, kFirstBits3 = 6.5f, kLeastBits = 5.0f, kFloatBits = 20.0f;
 constexpr double kLeft = 1e-3;
@@ -1895,6 +1897,12 @@ struct Team {
     const double rt = sqrt(ratio);
     return (float)log2((rt + 1.0) / (rt - 1.0));
   }
+  // Largest reduction factor of n sweeps on [1 / ratio, 1] over [low, 1].
+  __device__ __forceinline__ double cheb_reduction(double ratio, double low, int n) const {
+    const double c = 1.0 + 1.0 / ratio, r = 1.0 - 1.0 / ratio;
+    const double x0 = c / r, x = fmax(1.0, (c - 2.0 * low) / r);
+    return cosh(n * acosh(x)) / cosh(n * acosh(x0));
+  }
   // Weights of a defect correction into the omega table from row 1 on.  Between
   // two workgroup barriers.
   __device__ __forceinline__ void cheb_weights(double low, double lmax, int n) const {
@@ -2611,21 +2619,18 @@ __global__ __launch_bounds__(BLOCK) void st_team_kernel(const LevelDev* __restri
             do_step<kStepSpectrum>(tm, io, &calls, smem_dyn, red, omega_tab);
             lmax0 = uni(io.dmax);
             low0 = uni(io.resid);
-            if (low0 > 0.0 && lmax0 > low0 && lmax0 < 100.0 * low0) {
+            if (low0 > 0.0 && lmax0 > low0 && lmax0 < kWidest * low0) {
               // The interval is the spectrum's and never narrower by itself:
               // corrections do not see the modes left out, and slabs would be
               // accepted with their error.  A level's own sweeps and ratio are
-              // taken where they contract; where they do not they are GMRES's.
+              // taken where they contract the whole spectrum; else they are GMRES's.
               const double own = L->own_ratio > 0.0 ? L->own_ratio : lmax0 / low0;
-              const int n = L->own_sweeps > 0 ? tm.odd_or_even(max(L->own_sweeps, 3)) : 0;
-              decay = tm.cheb_decay(own);
               fixed = 0;
-              if (n == 0 || exp2f(1.0f - L->own_sweeps * decay) <= (float)kContract) {
+              if (L->own_sweeps > 0 && tm.cheb_reduction(own, low0 / lmax0, L->own_sweeps) <= kContract) {
                 low0 = lmax0 / own;
-                fixed = n;
-              } else {
-                decay = tm.cheb_decay(lmax0 / low0);
+                fixed = tm.odd_or_even(max(L->own_sweeps, 3));
               }
+              decay = tm.cheb_decay(lmax0 / low0);
               nc = fixed ? fixed : tm.cheb_degree(decay, DIM == 2 ? kFirstBits2 : kFirstBits3);
               tm.cheb_weights(low0, lmax0, nc);
               defect = cheb = true;

@@ -146,8 +146,10 @@ def test_result_with_a_guess_does_not_depend_on_the_batch(shape, precision):
     dict(shape=(17, 17), m=24, ic_kind="gauss", ic_radius=0.5), dict(shape=(17, 17), m=16, sigma_f0=0.1),
     dict(shape=(9, 9, 5), m=24), dict(shape=(9, 9, 9), m=16, theta=0.5, ic_kind="gauss", ic_radius=0.5),
     dict(shape=(17, 17), m=8, tuning=(13, 9.0)), dict(shape=(9, 9, 5), m=8, tuning=(20, 20.0)),
-    # settings that do not contract by themselves are for GMRES only
+    # settings that do not contract the whole spectrum are for GMRES only
     dict(shape=(17, 17), m=16, tuning=(3, 30.0)), dict(shape=(9, 9, 5), m=16, tuning=(4, 10.0)),
+    dict(shape=(17, 17), m=16, tuning=(30, 2.0)), dict(shape=(9, 9, 5), m=16, tuning=(30, 3.0), sigma_f0=2e-4),
+    dict(shape=(9, 20, 8), m=10, tuning=(30, 3.0), theta=0.5, sigma_f0=2e-4, T=0.008),
 ])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_corrections_leave_a_thousandth_of_the_newton_tolerance(c, precision):
@@ -155,7 +157,7 @@ def test_corrections_leave_a_thousandth_of_the_newton_tolerance(c, precision):
     contraction seen, which m slabs can add up to m 1e-13."""
     import torch
     from paper_1911_06066_amd import Context
-    kw = {k: c[k] for k in ("theta", "ic_kind", "ic_radius", "sigma_f0") if k in c}
+    kw = {k: c[k] for k in ("theta", "ic_kind", "ic_radius", "sigma_f0", "T") if k in c}
     wl, sig = _setup(c["shape"], c["m"], c.get("S", 1), precision, **kw)
     over = dict(level_tuning=[c["tuning"]]) if "tuning" in c else {}
     with Context(wl, team_size=c.get("G", 1), **over) as ctx:
