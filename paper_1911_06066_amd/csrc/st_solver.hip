@@ -169,8 +169,11 @@ constexpr int kMaxCorrections = 16;  // per slab
 // A slab is accepted with an error of kLeft newton_tol.  Drawn solves are then 8e-14 off
 // in the median, 5e-13 at most, with newton_tol 1e-10; kLeft 1e-5 makes it 9e-16
 // and 2e-15 for 1.11 of the time.
-// Corrections are for spectra up to kWidest.
-constexpr double kWidest = 100.0;
+// Corrections are for spectra up to kWidest: 48 sweeps give 7 bits there.  7x33 nodes
+// x 10 steps, 5 samples, lmax about 100 times the smallest eigenvalue, mixed: 7.5 ms,
+// 16.9 by GMRES alone (float32 sweeps lose too much to rounding on the widest
+// spectra; such slabs end in GMRES).
+constexpr double kWidest = 300.0;
 constexpr int kMaxDegree = 48;
 constexpr float kFirstBits2 = 10.0f, kFirstBits3 = 6.5f, kLeastBits = 5.0f, kFloatBits = 20.0f;
 constexpr double kLeft = 1e-3;

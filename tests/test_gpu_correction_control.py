@@ -182,3 +182,19 @@ def test_corrections_contract_on_anisotropic_grids(shape, kw):
     U_ref, _ = oapi.st_solve(wl, 0, sig, mode="timestep")
     assert np.abs(u.cpu().numpy() - U_ref).max() < 1e-9
     assert st[0]["krylov_iters"] == st[0]["newton_iters"] <= 6 * m
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_wide_spectra(precision):
+    """lmax is 140 times the smallest eigenvalue.  In float64 corrections of up to 48
+    sweeps do, six a slab at most; float32 sweeps lose too much to rounding, and
+    slabs may end in GMRES, with the same result."""
+    import torch
+    from paper_1911_06066_amd import Context
+    wl, sig = _setup((7, 33), 10, 2, precision, theta=0.75, sigma_f0=0.8, T=0.72, k_react=3.0)
+    with Context(wl, team_size=3) as ctx:
+        u, stats = ctx.st_solve(0, torch.from_numpy(sig).cuda())
+    U_ref, _ = oapi.st_solve(wl, 0, sig, mode="timestep")
+    assert np.abs(u.cpu().numpy() - U_ref).max() < 1e-9
+    if precision == "fp64":
+        assert all(s["krylov_iters"] == s["newton_iters"] <= 60 for s in stats)
