@@ -35,7 +35,7 @@ TUNING_DIR = os.path.join(HERE, "tuning")
 # error that its corrections do not see, so it is taken only if its solutions
 # are within AGREE of the first candidate's.
 CANDIDATES = [(0, 0.0), (11, 7.0), (13, 9.0)]
-CANDIDATES_3D = [(0, 0.0), (12, 7.0), (20, 20.0)]
+CANDIDATES_3D = [(0, 0.0), (16, 12.0), (20, 20.0)]
 AGREE = 1e-11  # a tenth of the default newton_tol
 TEAM_SIZES = (1, 2, 3, 4, 6, 8, 10, 12, 16, 24, 32)
 MAX_TEAM = 32
